@@ -26,26 +26,197 @@ struct MaxU32 {
 };
 
 // ---------------------------------------------------------------------------
-// Farthest point sampling, one workgroup of NT threads per cloud. Thread t
-// keeps points t, t + NT, ... (PPT of them) and their distance to the samples
-// taken so far in registers. Each step: update those distances with the last
-// sample and take the thread's farthest point (the lowest index among equals:
-// the thread's points come in index order and only a strictly larger distance
-// replaces); then the wave's: the maximum distance over the wave, the lanes
-// holding it by ballot, and among several such lanes the lowest index (rare:
-// a second reduction over the indices); then the workgroup's through one LDS
-// slot per wave. TAB (clouds of up to kFpsTab points): the cloud's
-// coordinates sit in an LDS table, and the winner's are read from it by
-// index; otherwise each thread also carries its farthest point's coordinates
-// and the winning lane writes them to its slot. The slots alternate between
-// two buffers so that one barrier per step suffices: step s+2 writes the
-// buffer step s read only after every wave has passed the barrier of step
-// s+1, which follows those reads.
+// Farthest point sampling.
+//
+// The method takes npoint sequential steps, each an argmax over the cloud of
+// the distance to the samples taken so far. A step is bound by the instructions
+// of its serial chain (the maximum, the winner's coordinates), issued by few
+// waves, and in a workgroup by its barrier and LDS round trips:
+//
+//  * pv_fps_wave_kernel (small clouds): one wave holds the whole cloud, NS
+//    points a lane.
+//  * pv_fps_step_kernel (few samples): a workgroup, a barrier per sample.
+//  * pv_fps_batch_kernel: distances only decrease, so if C holds every point
+//    whose distance exceeds T, then as long as the farthest point of C is
+//    farther than T it is the farthest point of the cloud, whatever the other
+//    points' distances have become. Each round the workgroup collects such a C
+//    (at most kFpsCand points), one wave takes samples from C in registers, up
+//    to 64 of them, until its farthest is no farther than T, and then the whole
+//    cloud is updated with the round's samples at once. Rooms of 8192 points
+//    take 1024 samples in about 50 rounds. The points are sorted along a
+//    Morton curve first, so that a wave's 64 lanes hold a compact cluster, and
+//    a cluster is updated only with the samples closer to its box than the
+//    farthest point of the cloud (about 10 of 128 clusters a sample; with each
+//    cluster's own farthest point 8.5, which does not pay for a reduction per
+//    cluster). An update that is skipped cannot change a minimum, so the
+//    samples are the method's own.
+//
+// Ties go to the lower index: every point of C carries its index. If more
+// points than C holds are equally far (a lattice), C takes the lowest indices
+// among them, T being the value just below theirs.
 // ---------------------------------------------------------------------------
+constexpr int kFpsCand = 128;       // candidates a round can hold: two a lane
+constexpr int kFpsTarget = 48;      // and aims at: one a lane
+constexpr int kFpsCells = 16 * 16 * 16;
+
+__device__ __forceinline__ float readlane_f(float v, int l) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+// A distance as its bits: distances are >= 0, so their bits order as their
+// values, and "no point" is a negative integer.
+__device__ __forceinline__ int nearer(int d, float x, float y, float z, float sx, float sy,
+                                      float sz) {
+    return min(d, __float_as_int(sqdist(x, y, z, sx, sy, sz)));
+}
+constexpr int kFpsNoPoint = -1;
+constexpr int kFpsUnset = 0x7f800000;  // +infinity
+
+// The largest of the wave's distances, at least 0 (wave-uniform).
+__device__ __forceinline__ int wave_farthest(int m) {
+    return (int)wave_reduce((uint32_t)max(m, 0), MaxU32{});
+}
+
+template <int NS>
+__global__ __launch_bounds__(64) void pv_fps_wave_kernel(const float* __restrict__ xyz, int N,
+                                                         int npoint, int32_t* __restrict__ idx,
+                                                         float* __restrict__ new_xyz) {
+    const int b = blockIdx.x, lane = threadIdx.x;
+    const float* p = xyz + (size_t)b * N * 3;
+    float x[NS], y[NS], z[NS];
+    int d[NS];
+#pragma unroll
+    for (int k = 0; k < NS; k++) {
+        const int j = lane + k * 64;
+        const float* q = p + (size_t)(j < N ? j : 0) * 3;
+        x[k] = q[0];
+        y[k] = q[1];
+        z[k] = q[2];
+        d[k] = j < N ? kFpsUnset : kFpsNoPoint;
+    }
+    float sx = p[0], sy = p[1], sz = p[2];
+    int pick = 0;  // lane l: the l-th sample of 64
+    for (int s = 0;;) {
+        // the samples' indices gather in the lanes and are stored 64 at a time
+        if ((s & 63) == 63 || s == npoint - 1) {
+            const int at = (s & ~63) + lane;
+            if (at <= s) {
+                idx[(size_t)b * npoint + at] = pick;
+                if (new_xyz) {
+                    const float* q = p + (size_t)pick * 3;
+                    float* o = new_xyz + ((size_t)b * npoint + at) * 3;
+                    o[0] = q[0];
+                    o[1] = q[1];
+                    o[2] = q[2];
+                }
+            }
+        }
+        if (++s >= npoint) break;
+        // each lane's farthest point, the lowest index among equals (a strictly
+        // larger distance replaces), then the wave's
+        d[0] = nearer(d[0], x[0], y[0], z[0], sx, sy, sz);
+        int m = d[0], mk = 0;
+#pragma unroll
+        for (int k = 1; k < NS; k++) {
+            d[k] = nearer(d[k], x[k], y[k], z[k], sx, sy, sz);
+            const bool more = d[k] > m;
+            m = more ? d[k] : m;
+            mk = more ? k : mk;
+        }
+        const int top = wave_farthest(m);
+        uint64_t hold = __ballot(m == top);
+        if ((hold & (hold - 1ull)) != 0ull) {  // several lanes: the lowest index
+            const uint32_t low = m == top ? 0xffffffffu - (uint32_t)(lane + mk * 64) : 0u;
+            const uint32_t lowest = wave_reduce(low, MaxU32{});  // in every lane
+            hold = __ballot(low == lowest);
+        }
+        if (hold == 0ull) hold = 1ull;  // not a number: some point of the cloud
+        const int l = __ffsll((long long)hold) - 1;
+        const int wk = __builtin_amdgcn_readlane(mk, l);
+#pragma unroll
+        for (int k = 0; k < NS; k++)
+            if (wk == k) {
+                sx = readlane_f(x[k], l);
+                sy = readlane_f(y[k], l);
+                sz = readlane_f(z[k], l);
+            }
+        pick = lane == (s & 63) ? min(l + wk * 64, N - 1) : pick;
+    }
+}
+
+// Samples from the candidates until none is farther than T; returns how many.
+// Lane n gets the n-th sample's place among the candidates.
+template <int NS>
+__device__ __forceinline__ int fps_take(const float4* s_c, const int* s_ci, int count, int T,
+                                        int most, int lane, int& pick) {
+    float x[NS], y[NS], z[NS];
+    int d[NS], j[NS];
+#pragma unroll
+    for (int k = 0; k < NS; k++) {
+        const float4 v = s_c[lane + k * 64];
+        x[k] = v.x;
+        y[k] = v.y;
+        z[k] = v.z;
+        d[k] = lane + k * 64 < count ? __float_as_int(v.w) : kFpsNoPoint;
+        j[k] = s_ci[lane + k * 64];
+    }
+    // ~45 instructions in one dependent chain, ~390 cycles a sample
+    int n = 0;
+    do {
+        bool second = false;
+        int m = d[0];
+        if constexpr (NS == 2) {
+            second = d[1] > d[0];
+            m = max(d[0], d[1]);
+        }
+        const int top = wave_farthest(m);
+        if (top <= T) break;
+        uint64_t hold = __ballot(m == top);
+        uint64_t many = hold & (hold - 1ull);
+        if constexpr (NS == 2) many |= __ballot(m == top && d[0] == d[1]);
+        if (__builtin_expect(many != 0ull, 0)) {  // equal distances: the lowest index
+            uint32_t low = d[0] == top ? 0xffffffffu - (uint32_t)j[0] : 0u;
+            if constexpr (NS == 2)
+                low = max(low, d[1] == top ? 0xffffffffu - (uint32_t)j[1] : 0u);
+            const uint32_t lowest = wave_reduce(low, MaxU32{});
+            hold = __ballot(low == lowest);
+            if constexpr (NS == 2)
+                second = d[1] == top && 0xffffffffu - (uint32_t)j[1] == lowest;
+        }
+        const int l = __builtin_ctzll(hold);  // not empty: top is some lane's
+        float sx = readlane_f(x[0], l), sy = readlane_f(y[0], l), sz = readlane_f(z[0], l);
+        int at = l;
+        if constexpr (NS == 2) {
+            const bool up = (__ballot(second) >> l) & 1ull;
+            const float ux = readlane_f(x[1], l), uy = readlane_f(y[1], l),
+                        uz = readlane_f(z[1], l);
+            sx = up ? ux : sx;
+            sy = up ? uy : sy;
+            sz = up ? uz : sz;
+            at = up ? l + 64 : l;
+        }
+        pick = lane == n ? at : pick;
+#pragma unroll
+        for (int k = 0; k < NS; k++) d[k] = nearer(d[k], x[k], y[k], z[k], sx, sy, sz);
+    } while (++n < most);
+    return n;
+}
+
+// One workgroup of NT threads per cloud, step by step. Thread t keeps points t,
+// t + NT, ... (PPT of them) and their distance to the samples taken so far in
+// registers. Each step: update those distances with the last sample and take
+// the thread's farthest point (the lowest index among equals: the thread's
+// points come in index order and only a strictly larger distance replaces);
+// then the wave's; then the workgroup's through one LDS slot per wave. TAB
+// (clouds of up to kFpsTab points): the cloud's coordinates sit in an LDS
+// table, and the winner's are read from it by index; otherwise each thread also
+// carries its farthest point's coordinates and the winning lane writes them to
+// its slot. The slots alternate between two buffers so that one barrier per
+// step suffices: step s+2 writes the buffer step s read only after every wave
+// has passed the barrier of step s+1, which follows those reads.
 constexpr int kFpsTab = 8192;
 
 template <int PPT, int NT, bool TAB>
-__global__ __launch_bounds__(NT) void pv_fps_kernel(const float* __restrict__ xyz, int N,
+__global__ __launch_bounds__(NT) void pv_fps_step_kernel(const float* __restrict__ xyz, int N,
                                                     int npoint, int32_t* __restrict__ idx,
                                                     float* __restrict__ new_xyz) {
     constexpr int NW = NT / 64;
@@ -158,6 +329,312 @@ __global__ __launch_bounds__(NT) void pv_fps_kernel(const float* __restrict__ xy
                 oxyz[(size_t)s * 3 + 2] = lz;
             }
         }
+    }
+}
+
+// Order-preserving map of a float's bits to u32 (any finite value maps above 0).
+__device__ __forceinline__ uint32_t f32_key(float v) {
+    const uint32_t u = __float_as_uint(v);
+    return u ^ ((u >> 31) ? 0xffffffffu : 0x80000000u);
+}
+__device__ __forceinline__ float f32_unkey(uint32_t k) {
+    return __uint_as_float(k ^ ((k >> 31) ? 0x80000000u : 0xffffffffu));
+}
+// Bits 0..3 of v spread to every third bit.
+__device__ __forceinline__ uint32_t spread4(uint32_t v) {
+    return (v & 1u) | ((v & 2u) << 2) | ((v & 4u) << 4) | ((v & 8u) << 6);
+}
+
+template <int PPT, int NT>
+__global__ __launch_bounds__(NT) void pv_fps_batch_kernel(const float* __restrict__ xyz, int N,
+                                                          int npoint, int32_t* __restrict__ idx,
+                                                          float* __restrict__ new_xyz) {
+    constexpr int NW = NT / 64;
+    static_assert(PPT % 2 == 0 && NW <= 16 && PPT * NT <= 65536, "slot pairs, u16 indices");
+    __shared__ uint32_t s_cell[kFpsCells];
+    __shared__ uint16_t s_order[PPT * NT];
+    __shared__ float4 s_cand[kFpsCand];
+    __shared__ int s_cand_i[kFpsCand];
+    __shared__ float4 s_pick[64];
+    __shared__ float4 s_box[PPT * NW][2];  // a cluster's lower, upper corner
+    __shared__ uint32_t s_red[NW][6];
+    __shared__ int s_far[NW];
+    __shared__ int s_count[3];
+    __shared__ int s_npick;
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const float* p = xyz + (size_t)b * N * 3;
+
+    // --- the cloud's box, then its points in Morton order of a 16^3 grid over
+    // it (a counting sort; the order inside a cell does not matter)
+    if (tid < 3) s_count[tid] = 0;
+    float px[PPT], py[PPT], pz[PPT];
+    for (int c = tid; c < kFpsCells; c += NT) s_cell[c] = 0u;
+    uint32_t box[6] = {0u, 0u, 0u, 0u, 0u, 0u};  // keys of max(-x), .., max(x), ..
+#pragma unroll 4
+    for (int k = 0; k < PPT; k++) {
+        const int j = tid + k * NT;
+        const float* q = p + (size_t)(j < N ? j : 0) * 3;
+        const float x = q[0], y = q[1], z = q[2];
+        box[0] = max(box[0], f32_key(-x));
+        box[1] = max(box[1], f32_key(-y));
+        box[2] = max(box[2], f32_key(-z));
+        box[3] = max(box[3], f32_key(x));
+        box[4] = max(box[4], f32_key(y));
+        box[5] = max(box[5], f32_key(z));
+    }
+#pragma unroll
+    for (int a = 0; a < 6; a++) {
+        const uint32_t m = wave_reduce(box[a], MaxU32{});
+        if (lane == 0) s_red[w][a] = m;
+    }
+    pv_lds_barrier();
+#pragma unroll
+    for (int a = 0; a < 6; a++) {
+        uint32_t m = s_red[0][a];
+        for (int i = 1; i < NW; i++) m = max(m, s_red[i][a]);
+        box[a] = m;
+    }
+    const float lox = -f32_unkey(box[0]), loy = -f32_unkey(box[1]), loz = -f32_unkey(box[2]);
+    const float ext = fmaxf(fmaxf(f32_unkey(box[3]) - lox, f32_unkey(box[4]) - loy),
+                            f32_unkey(box[5]) - loz);
+    const float scale = 16.f / ext;
+#pragma unroll
+    for (int k = 0; k < PPT; k++) {  // read again rather than held: registers
+        const int j = tid + k * NT;
+        const float* q = p + (size_t)(j < N ? j : 0) * 3;
+        px[k] = q[0];
+        py[k] = q[1];
+        pz[k] = q[2];
+    }
+    uint32_t place[PPT];  // cell << 16 | rank within it
+#pragma unroll
+    for (int k = 0; k < PPT; k++) {
+        // clamped, so that any coordinate falls in some cell (NaN: cell 0)
+        const float fx = fminf(fmaxf((px[k] - lox) * scale, 0.f), 15.f);
+        const float fy = fminf(fmaxf((py[k] - loy) * scale, 0.f), 15.f);
+        const float fz = fminf(fmaxf((pz[k] - loz) * scale, 0.f), 15.f);
+        const uint32_t c = spread4((uint32_t)fx) | (spread4((uint32_t)fy) << 1) |
+                           (spread4((uint32_t)fz) << 2);
+        place[k] = c << 16;
+        if (tid + k * NT < N) place[k] += atomicAdd(&s_cell[c], 1u);
+    }
+    pv_lds_barrier();
+    {
+        constexpr int E = kFpsCells / NT;
+        uint32_t v[E], sum = 0u;
+#pragma unroll
+        for (int e = 0; e < E; e++) {
+            v[e] = s_cell[tid * E + e];
+            sum += v[e];
+        }
+        uint32_t incl = sum;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t o = (uint32_t)__shfl_up((int)incl, off, 64);
+            if (lane >= off) incl += o;
+        }
+        if (lane == 63) s_red[w][0] = incl;  // every wave has read its box
+        pv_lds_barrier();
+        uint32_t base = incl - sum;
+        for (int i = 0; i < w; i++) base += s_red[i][0];
+#pragma unroll
+        for (int e = 0; e < E; e++) {
+            s_cell[tid * E + e] = base;
+            base += v[e];
+        }
+    }
+    pv_lds_barrier();
+#pragma unroll
+    for (int k = 0; k < PPT; k++) {
+        const int j = tid + k * NT;
+        if (j < N) s_order[s_cell[place[k] >> 16] + (place[k] & 0xffffu)] = (uint16_t)j;
+    }
+    pv_lds_barrier();
+
+    // --- slot k of wave w: the 64 points of cluster k * NW + w (neighbouring
+    // clusters in different waves)
+    int d[PPT];
+    const float fx0 = p[0], fy0 = p[1], fz0 = p[2];
+#pragma unroll
+    for (int k = 0; k < PPT; k++) {
+        const int pos = (k * NW + w) * 64 + lane;
+        const float* q = p + (size_t)(pos < N ? s_order[pos] : 0) * 3;
+        px[k] = q[0];
+        py[k] = q[1];
+        pz[k] = q[2];
+    }
+    int wfar = 0;
+#pragma unroll
+    for (int k = 0; k < PPT; k++) {
+        const int c0 = (k * NW + w) * 64;  // wave-uniform
+        d[k] = kFpsNoPoint;
+        if (c0 >= N) continue;
+        const bool ok = c0 + lane < N;
+        if (ok) d[k] = nearer(kFpsUnset, px[k], py[k], pz[k], fx0, fy0, fz0);
+        wfar = max(wfar, d[k]);
+        auto least = [&](float v) {
+            return -f32_unkey(wave_reduce(ok ? f32_key(-v) : 0u, MaxU32{}));
+        };
+        auto most = [&](float v) {
+            return f32_unkey(wave_reduce(ok ? f32_key(v) : 0u, MaxU32{}));
+        };
+        const float4 lo = make_float4(least(px[k]), least(py[k]), least(pz[k]), 0.f);
+        const float4 hi = make_float4(most(px[k]), most(py[k]), most(pz[k]), 0.f);
+        if (lane == 0) {
+            s_box[k * NW + w][0] = lo;
+            s_box[k * NW + w][1] = hi;
+        }
+    }
+    if (tid == 0) {
+        idx[(size_t)b * npoint] = 0;
+        if (new_xyz) {
+            float* o = new_xyz + (size_t)b * npoint * 3;
+            o[0] = fx0;
+            o[1] = fy0;
+            o[2] = fz0;
+        }
+    }
+
+    // --- rounds
+    float below = 0.1f;  // T = (1 - below) * the largest distance
+    int turn = 0;        // s_count[turn] counts the current candidates
+    for (int s = 1; s < npoint;) {
+        wfar = wave_farthest(wfar);
+        if (lane == 0) s_far[w] = wfar;
+        pv_lds_barrier();
+        int top = s_far[0];
+#pragma unroll
+        for (int i = 1; i < NW; i++) top = max(top, s_far[i]);
+        top = __builtin_amdgcn_readfirstlane(top);
+        if (top == 0) {  // every point coincides with a sample: the lowest index
+            for (int t = s + tid; t < npoint; t += NT) {
+                const size_t o = (size_t)b * npoint + t;
+                idx[o] = 0;
+                if (new_xyz) {
+                    new_xyz[o * 3] = fx0;
+                    new_xyz[o * 3 + 1] = fy0;
+                    new_xyz[o * 3 + 2] = fz0;
+                }
+            }
+            return;  // the whole workgroup: `top` is uniform
+        }
+        const float ftop = __int_as_float(top);
+        // T >= 0, at most the value just below the largest distance
+        int T = min(__float_as_int(ftop * (1.f - below)), top - 1);
+        bool tie = T == top - 1;
+        int jmax = N, jlo = -1, jhi = N - 1, count = 0;
+        // Collect; with too many candidates raise T, and once T is just below
+        // the largest distance halve the range of indices instead. Both end:
+        // the first within 12 turns, and the count grows by at most one with
+        // each index.
+        for (int t = 0; t < 40; t++) {
+            uint64_t in[PPT];
+            int n = 0;
+#pragma unroll
+            for (int k = 0; k < PPT; k++) {
+                bool c = d[k] > T;  // no point: negative
+                if (jmax < N) c = c && s_order[(k * NW + w) * 64 + lane] <= jmax;
+                in[k] = __ballot(c);
+                n += __popcll(in[k]);
+            }
+            if (n > 0) {
+                int base = 0;
+                if (lane == 0) base = atomicAdd(&s_count[turn], n);
+                base = __builtin_amdgcn_readfirstlane(base);
+#pragma unroll
+                for (int k = 0; k < PPT; k++) {
+                    if (in[k] == 0ull) continue;
+                    const int at = base + __popcll(in[k] & ((1ull << lane) - 1ull));
+                    if (((in[k] >> lane) & 1ull) && at < kFpsCand) {
+                        s_cand[at] = make_float4(px[k], py[k], pz[k], __int_as_float(d[k]));
+                        s_cand_i[at] = s_order[(k * NW + w) * 64 + lane];
+                    }
+                    base += __popcll(in[k]);
+                }
+            }
+            pv_lds_barrier();
+            count = __builtin_amdgcn_readfirstlane(s_count[turn]);
+            turn = turn == 2 ? 0 : turn + 1;
+            // the count after the next: every wave read it before this barrier
+            if (tid == 0) s_count[turn == 2 ? 0 : turn + 1] = 0;
+            if (count > 0 && count <= kFpsCand) break;
+            if (!tie) {
+                below *= 0.35f;
+                T = min(__float_as_int(ftop * (1.f - below)), top - 1);
+                if (t >= 10) T = top - 1;
+                tie = T == top - 1;
+            } else {
+                if (jmax == N) jmax = N - 1;
+                if (count == 0) jlo = jmax;
+                else jhi = jmax;
+                jmax = (jlo + jhi) >> 1;
+            }
+        }
+        count = min(count, kFpsCand);
+        if (w == 0) {
+            int pick = 0;
+            const int most = min(64, npoint - s);
+            const int n = count <= 64 ? fps_take<1>(s_cand, s_cand_i, count, T, most, lane, pick)
+                                      : fps_take<2>(s_cand, s_cand_i, count, T, most, lane, pick);
+            float4 v = s_cand[pick];
+            v.w = __int_as_float(s_cand_i[pick]);
+            s_pick[lane] = v;
+            if (lane == 0) s_npick = n;
+        }
+        // aim at kFpsTarget candidates in the next round
+        const float ratio = sqrtf((float)kFpsTarget / (float)max(count, 1));
+        below = fminf(0.9f, fmaxf(1e-6f, below * fminf(2.f, fmaxf(0.5f, ratio))));
+        pv_lds_barrier();
+        const int np = __builtin_amdgcn_readfirstlane(s_npick);
+        if (np == 0) return;  // cannot be: a candidate is farther than T
+        if (w == NW - 1 && lane < np) {
+            const float4 v = s_pick[lane];
+            const size_t o = (size_t)b * npoint + s + lane;
+            idx[o] = __float_as_int(v.w);
+            if (new_xyz) {
+                new_xyz[o * 3] = v.x;
+                new_xyz[o * 3 + 1] = v.y;
+                new_xyz[o * 3 + 2] = v.z;
+            }
+        }
+        s += np;
+        if (s >= npoint) return;
+        // Update each cluster with the samples that can reach it: 32 samples
+        // against two clusters at once, one in each half of the wave. The
+        // distance to the box and the points' own distances are rounded apart:
+        // a margin of 2e-5 (and an absolute one, for squares that underflow)
+        // keeps every sample that could change a minimum, and so does an
+        // overflow or what is not a number.
+        const float reach = (ftop + 1e-36f) * (1.f + 2e-5f);
+        for (int p0 = 0; p0 < np; p0 += 32) {
+            const float4 pk = s_pick[p0 + (lane & 31)];
+            const bool some = p0 + (lane & 31) < np;
+#pragma unroll
+            for (int k = 0; k < PPT / 2; k++) {
+                // read the box here, not ahead of the loops (registers)
+                asm volatile("" ::: "memory");
+                const int c = (lane < 32 ? k : k + PPT / 2) * NW + w;
+                const float4 lo = s_box[c][0], hi = s_box[c][1];
+                const float ex = fmaxf(fmaxf(lo.x - pk.x, pk.x - hi.x), 0.f);
+                const float ey = fmaxf(fmaxf(lo.y - pk.y, pk.y - hi.y), 0.f);
+                const float ez = fmaxf(fmaxf(lo.z - pk.z, pk.z - hi.z), 0.f);
+                const float e2 = ex * ex + ey * ey + ez * ez;
+                const uint64_t near = __ballot(some && !(e2 >= reach && e2 <= 3e38f));
+                auto pass = [&](int kk, uint32_t m) {
+                    while (m != 0u) {
+                        const int l = __ffs((int)m) - 1;
+                        m &= m - 1u;
+                        d[kk] = nearer(d[kk], px[kk], py[kk], pz[kk], readlane_f(pk.x, l),
+                                       readlane_f(pk.y, l), readlane_f(pk.z, l));
+                    }
+                };
+                pass(k, (uint32_t)near);
+                pass(k + PPT / 2, (uint32_t)(near >> 32));
+            }
+        }
+        wfar = 0;
+#pragma unroll
+        for (int k = 0; k < PPT; k++) wfar = max(wfar, d[k]);
     }
 }
 
@@ -404,18 +881,29 @@ unsigned grid_for(size_t total) {
 pvconv_status pv_launch_fps(const float* xyz, int B, int N, int npoint, int32_t* idx,
                             float* new_xyz, hipStream_t s) {
     if (B == 0) return PVCONV_OK;
-    // four waves (one per SIMD), so that each step's wave reductions are
-    // paid four times, not sixteen; the clouds' points in registers
-#define PV_FPS(PPT, NT, TAB)                                                              \
-    hipLaunchKernelGGL((pv_fps_kernel<PPT, NT, TAB>), dim3(B), dim3(NT), 0, s, xyz, N, npoint, \
-                       idx, new_xyz)
-    if (N <= 256) PV_FPS(4, 64, true);
-    else if (N <= 1024) PV_FPS(4, 256, true);
-    else if (N <= 2048) PV_FPS(8, 256, true);
-    else if (N <= 4096) PV_FPS(16, 256, true);
-    else if (N <= kFpsTab) PV_FPS(32, 256, true);
-    else if (N <= kPvFpsMaxN) PV_FPS(16, 1024, false);
-    else return PVCONV_ENOTSUP;
+#define PV_FPS(NT, ...)                                                                  \
+    hipLaunchKernelGGL((__VA_ARGS__), dim3(B), dim3(NT), 0, s, xyz, N, npoint, idx, new_xyz)
+    if (N > kPvFpsMaxN) return PVCONV_ENOTSUP;
+    if (N <= 64) PV_FPS(64, pv_fps_wave_kernel<1>);
+    else if (N <= 128) PV_FPS(64, pv_fps_wave_kernel<2>);
+    else if (N <= 256) PV_FPS(64, pv_fps_wave_kernel<4>);
+    else if (N <= 512) PV_FPS(64, pv_fps_wave_kernel<8>);
+    // The rounds cost a sort (~10 us) and yield one to three samples each at
+    // first: up to 64 samples the plain steps are as fast or faster (us, four
+    // clouds: 8192 -> 32 points 39 against 68, -> 64 points 72 against 84,
+    // -> 1024 points 1080 against 365).
+    else if (npoint <= 64) {
+        if (N <= 1024) PV_FPS(256, pv_fps_step_kernel<4, 256, true>);
+        else if (N <= 2048) PV_FPS(256, pv_fps_step_kernel<8, 256, true>);
+        else if (N <= 4096) PV_FPS(256, pv_fps_step_kernel<16, 256, true>);
+        else if (N <= kFpsTab) PV_FPS(256, pv_fps_step_kernel<32, 256, true>);
+        else PV_FPS(1024, pv_fps_step_kernel<16, 1024, false>);
+    }
+    else if (N <= 1024) PV_FPS(256, pv_fps_batch_kernel<4, 256>);
+    else if (N <= 2048) PV_FPS(512, pv_fps_batch_kernel<4, 512>);
+    else if (N <= 4096) PV_FPS(1024, pv_fps_batch_kernel<4, 1024>);
+    else if (N <= 8192) PV_FPS(1024, pv_fps_batch_kernel<8, 1024>);
+    else PV_FPS(1024, pv_fps_batch_kernel<16, 1024>);
 #undef PV_FPS
     return pv_launch_status();
 }

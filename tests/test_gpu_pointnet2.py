@@ -79,6 +79,43 @@ def test_fps_matches_oracle(B, N, npoint, cloud):
     np.testing.assert_array_equal(new_xyz.cpu().numpy(), oracle.gather_points(xyz, want))
 
 
+def _edge_cloud(kind, N):
+    rng = np.random.default_rng(N)
+    if kind == "lattice":  # distinct points, most distances shared by hundreds of them
+        n = int(np.ceil(N ** (1 / 3)))
+        g = np.stack(np.meshgrid(*[np.arange(n)] * 3, indexing="ij"), -1).reshape(-1, 3)
+        return rng.permutation(g[:N]).astype(np.float32)[None]
+    if kind == "tiny":  # squared distances below the normal range
+        return (rng.integers(-9, 10, size=(1, N, 3)) * 1e-21).astype(np.float32)
+    if kind == "line":  # one axis, far from the origin: coarse coordinates
+        xyz = np.full((1, N, 3), 7.0, np.float32)
+        xyz[..., 1] = 4096.0 + rng.random((1, N)) * 3.0
+        return xyz
+    assert kind == "outlier"  # one far point: all others in one cell of the sort
+    xyz = rng.random((1, N, 3)).astype(np.float32)
+    xyz[0, N // 2] = 1e4
+    return xyz
+
+
+@pytest.mark.parametrize("kind,N,npoint", [
+    # the edges of the kernels' ranges, and clouds whose ties exceed the
+    # candidates of a round, whose updates must not be skipped by a rounded
+    # bound, or whose points fall in one cell
+    ("line", 1, 1), ("line", 65, 65), ("outlier", 128, 60), ("lattice", 129, 129),
+    ("tiny", 512, 200), ("outlier", 513, 513), ("lattice", 1024, 700), ("tiny", 1025, 300),
+    ("line", 2049, 900), ("lattice", 4097, 1500), ("lattice", 13824, 2000), ("tiny", 8192, 500),
+    ("outlier", 8193, 600), ("line", 16384, 400),
+    # few samples: step by step
+    ("lattice", 600, 64), ("lattice", 2000, 33), ("outlier", 4096, 64), ("tiny", 8192, 64),
+    ("lattice", 9000, 50),
+])
+def test_fps_at_the_edges_of_its_kernels(kind, N, npoint):
+    xyz = _edge_cloud(kind, N)
+    want = oracle.fps(xyz, npoint)
+    got = pv.pvconv_furthest_point_sample(dev(xyz), npoint, want_xyz=False).cpu().numpy()
+    assert np.array_equal(got, want), np.argwhere(got != want)[:5]
+
+
 def test_fps_is_repeatable_and_takes_one_point():
     xyz = dev(_rooms(2, 5000, 1)[0])
     a = pv.pvconv_furthest_point_sample(xyz, 400, want_xyz=False)
