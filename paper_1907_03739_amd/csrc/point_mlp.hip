@@ -570,29 +570,83 @@ __device__ __forceinline__ void load8_raw(const uint16_t* p, float (&v)[8]) {
     }
 }
 
-template <typename XT>
+// fp32 weights: v_mfma_f32_32x32x2_f32 (fp32 products and sums), one workgroup
+// per 32 points x 32 channels, its four waves on alternate 8-deep pieces of K.
+// Weights are the A operand, points the B: lane l holds row l % 32 of either,
+// and its half l / 32 four consecutive values of K a piece, so both operands
+// are 16-byte loads straight from their rows and no layout work is left. The
+// loads' latency sets the time (16384 x 128 -> 64: 1.7 us of MFMAs), so K is
+// split over the waves rather than walked by one. The partial sums meet in LDS
+// and are added in wave order; wave w then finishes channels 8w .. 8w+7.
+// 16384 x 128 -> 64: 234 us with a thread per output element reading both
+// rows value by value, 9 us this way (four pieces in flight a wave: 9.3, and
+// 91 against 77 us at 8192 x 512 -> 512).
+template <typename XT, bool VEC>
+__device__ __forceinline__ void load4_f32(const XT* p, int valid, float (&v)[4]) {
+    if constexpr (VEC) {  // valid is 4 or at most 0
+        if constexpr (sizeof(XT) == 4) {
+            const float4 a = valid > 0 ? *(const float4*)p : make_float4(0.f, 0.f, 0.f, 0.f);
+            v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+        } else {
+            const uint2 a = valid > 0 ? *(const uint2*)p : make_uint2(0u, 0u);
+            v[0] = __uint_as_float(a.x << 16);
+            v[1] = __uint_as_float(a.x & 0xffff0000u);
+            v[2] = __uint_as_float(a.y << 16);
+            v[3] = __uint_as_float(a.y & 0xffff0000u);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; i++) v[i] = i < valid ? ld1<XT>(p + i) : 0.f;
+    }
+}
+
+template <typename XT, bool VEC>
 __global__ __launch_bounds__(256) void pv_point_mlp_f32_kernel(
     const XT* __restrict__ x, int x_ld, int M, int Cin, int Cout, const float* __restrict__ w,
     PvBnFold bn, int act, float slope, const float* __restrict__ cloud_bias, int ppc,
     const float* __restrict__ residual, int res_ld, void* __restrict__ out, int out_bf16,
     int out_ld) {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= (size_t)M * Cout) return;
-    const int n = (int)(i % Cout);
-    const size_t m = i / Cout;
-    const XT* xr = x + m * x_ld;
-    const float* wr = w + (size_t)n * Cin;
-    float s = 0.f;
-    for (int k = 0; k < Cin; k++) s += wr[k] * ld1<XT>(xr + k);
-    if (cloud_bias) s += cloud_bias[(m / ppc) * Cout + n];
-    float scale, shift;
-    pv_bn_coeffs(bn, n, scale, shift);
-    float v = pv_activate(s * scale + shift, act, slope);
-    if (residual) v += residual[m * res_ld + n];
-    if (out_bf16)
-        ((uint16_t*)out)[m * out_ld + n] = pv_f32_to_bf16(v);
-    else
-        ((float*)out)[m * out_ld + n] = v;
+    __shared__ float s_part[4][16][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int r = lane & 31, half = lane >> 5;
+    const int m = blockIdx.x * 32 + r, n0 = blockIdx.y * 32;
+    // rows past the end read the last row; their results are not stored
+    const XT* xr = x + (size_t)min(m, M - 1) * x_ld;
+    const float* wr = w + (size_t)min(n0 + r, Cout - 1) * Cin;
+    pv_f32x16 acc;
+#pragma unroll
+    for (int i = 0; i < 16; i++) acc[i] = 0.f;
+    for (int k0 = wv * 8; k0 < Cin; k0 += 32) {
+        const int k = k0 + half * 4;
+        float a[4], b[4];
+        load4_f32<float, VEC>(wr + k, Cin - k, a);
+        load4_f32<XT, VEC>(xr + k, Cin - k, b);
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 16; i++) s_part[wv][i][lane] = acc[i];
+    __syncthreads();
+    // lane l holds point l % 32; register i channel 8 (i / 4) + 4 (l / 32) + i % 4
+    if (m >= M) return;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const int n = n0 + 8 * wv + 4 * half + i;
+        if (n >= Cout) break;
+        float s = s_part[0][4 * wv + i][lane];
+#pragma unroll
+        for (int j = 1; j < 4; j++) s += s_part[j][4 * wv + i][lane];
+        if (cloud_bias) s += cloud_bias[(size_t)(m / ppc) * Cout + n];
+        float scale, shift;
+        pv_bn_coeffs(bn, n, scale, shift);
+        float v = pv_activate(s * scale + shift, act, slope);
+        if (residual) v += residual[(size_t)m * res_ld + n];
+        if (out_bf16)
+            ((uint16_t*)out)[(size_t)m * out_ld + n] = pv_f32_to_bf16(v);
+        else
+            ((float*)out)[(size_t)m * out_ld + n] = v;
+    }
 }
 
 template <int NB, typename XT>
@@ -872,16 +926,20 @@ pvconv_status pv_launch_point_mlp(const void* x, bool x_bf16, int x_ld, int M, i
                                       ppc, res, res_ld, out, out_bf16, out_ld, s);
         }
     } else {
-        const size_t total = (size_t)M * Cout;
-        const unsigned blocks = (unsigned)((total + 255) / 256);
-        if (x_bf16)
-            hipLaunchKernelGGL(pv_point_mlp_f32_kernel<uint16_t>, dim3(blocks), dim3(256), 0, s,
-                               (const uint16_t*)x, x_ld, M, Cin, Cout, (const float*)w, bn, act,
-                               slope, cb, ppc, res, res_ld, out, (int)out_bf16, out_ld);
-        else
-            hipLaunchKernelGGL(pv_point_mlp_f32_kernel<float>, dim3(blocks), dim3(256), 0, s,
-                               (const float*)x, x_ld, M, Cin, Cout, (const float*)w, bn, act,
-                               slope, cb, ppc, res, res_ld, out, (int)out_bf16, out_ld);
+        // four consecutive values of K are one aligned vector of either row
+        const bool vec = Cin % 4 == 0 && pv_aligned16(x) && pv_aligned16(w) &&
+                         x_ld % 4 == 0;
+        const dim3 g((M + 31) / 32, (Cout + 31) / 32);
+#define PV_F32(XT, V)                                                                         \
+    hipLaunchKernelGGL((pv_point_mlp_f32_kernel<XT, V>), g, dim3(256), 0, s, (const XT*)x, x_ld, \
+                       M, Cin, Cout, (const float*)w, bn, act, slope, cb, ppc, res, res_ld, out, \
+                       (int)out_bf16, out_ld)
+        if (x_bf16) {
+            if (vec) PV_F32(uint16_t, true); else PV_F32(uint16_t, false);
+        } else {
+            if (vec) PV_F32(float, true); else PV_F32(float, false);
+        }
+#undef PV_F32
     }
     return pv_launch_status();
 }

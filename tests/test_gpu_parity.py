@@ -569,6 +569,42 @@ def test_point_mlp_f32_matches_oracle(M, Cin, Cout):
     assert_dot_f32(host(out), ref, mag, "mlp fp32")
 
 
+@pytest.mark.parametrize("M,Cin,Cout,xdt,odt,ppc,off", [
+    # tiles of 32 points x 32 channels, K in pieces of 8 over four waves: one
+    # point, one value of K, ragged ends of each, K past one turn of the waves
+    (1, 1, 1, "f32", "f32", 0, 0), (31, 4, 33, "f32", "f32", 0, 0),
+    (33, 12, 31, "f32", "bf16", 0, 0), (64, 36, 64, "bf16", "f32", 32, 0),
+    (500, 130, 70, "f32", "f32", 250, 0), (257, 1000, 40, "f32", "f32", 0, 0),
+    (100, 64, 32, "f32", "f32", 0, 1),     # rows off 16-byte boundaries
+    (100, 64, 32, "bf16", "f32", 0, 1), (96, 20, 8, "bf16", "bf16", 0, 4),
+])
+def test_point_mlp_f32_edges_of_its_tiles(M, Cin, Cout, xdt, odt, ppc, off):
+    rng = np.random.default_rng(M * 7 + Cin)
+    x = rng.normal(size=(M, Cin)).astype(np.float32)
+    if xdt == "bf16":
+        x = bf16_round(x).astype(np.float32)
+    w = synth.kaiming_normal(rng, (Cout, Cin), Cin, bf16=False)
+    bias = rng.normal(size=Cout).astype(np.float32)
+    cb = rng.normal(size=(M // ppc, Cout)).astype(np.float32) if ppc else None
+    ref = oracle.linear(x.astype(np.float64), w, bias)
+    mag = np.abs(x.astype(np.float64)) @ np.abs(w.T.astype(np.float64)) + np.abs(bias)
+    if cb is not None:
+        ref = ref + np.repeat(cb, ppc, axis=0)
+        mag = mag + np.abs(np.repeat(cb, ppc, axis=0))
+    wide = torch.zeros((M, Cin + 8), dtype=torch.bfloat16 if xdt == "bf16" else torch.float32,
+                       device="cuda")
+    xd = wide[:, off:off + Cin]
+    xd.copy_(dev(x))
+    out = pv.pvconv_point_mlp(xd, dev(w), bias=dev(bias), act="leaky", slope=0.2,
+                              cloud_bias=dev(cb) if ppc else None, points_per_cloud=max(ppc, 1),
+                              out_dtype=torch.bfloat16 if odt == "bf16" else torch.float32)
+    ref = oracle.leaky_relu(ref, 0.2)
+    if odt == "bf16":
+        assert_bf16_step(host(out), ref, "mlp fp32, bf16 out")
+    else:
+        assert_dot_f32(host(out), ref, mag, "mlp fp32")
+
+
 @pytest.mark.parametrize("B,N,R,cin,cout,xdt,odt", [
     (2, 2048, 32, 64, 128, "f32", "f32"),    # part-seg layer's end, two clouds
     (3, 777, 16, 64, 96, "bf16", "f32"),     # ragged last tile, 96 = 1.5 channel blocks
