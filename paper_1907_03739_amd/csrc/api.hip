@@ -58,6 +58,7 @@ struct ForwardWs {
     void* grid_a;
     void* grid_b;
     float* devox;
+    uint8_t* d1;   // bits of the voxels the convolutions compute
     float* split;  // fp32 partial sums of split convolutions (small grids), or NULL
     size_t total;
 };
@@ -85,6 +86,7 @@ ForwardWs carve_forward(void* base, int B, int N, const pvconv_layer* L) {
     w.grid_a = take((size_t)B * V * cmax * es);
     w.grid_b = take((size_t)B * V * L->cout * es);
     w.devox = (float*)take((size_t)B * N * L->cout * 4);
+    w.d1 = (uint8_t*)take(pv_conv3d_rows_d1_bytes(B, L->R));
     size_t split = 0;
     if (L->compute_dt == PVCONV_BF16)
         for (int i = 0; i < L->n_convs; i++) {
@@ -590,16 +592,38 @@ pvconv_status pvconv_forward_ex(const float* coords, const void* feats, pvconv_d
     void* src = w.grid_a;
     void* dst = w.grid_b;
     int cin = L->cin;
-    // The last convolution's grid is read only by the devoxelisation, at
-    // its points' corners (trilinear) or voxels (nearest), all within one
-    // voxel of an occupied voxel: only those outputs are computed.
+    // The convolutions' grids are internal: the last one's is read only by
+    // the devoxelisation, at its points' corners (trilinear) or voxels
+    // (nearest), all within one voxel of an occupied voxel, so only those
+    // outputs are computed. With one or two convolutions the first one's
+    // output is also computed only there, and constant elsewhere.
+    const bool rows = bf && pv_conv3d_rows_ok(B, R, cin, L->cout, L->n_convs);
     for (int i = 0; i < L->n_convs; i++) {
         const bool last = i == L->n_convs - 1;
-        st = pv_launch_conv3d(src, B, R, cin, L->cout, L->conv_w[i],
-                              pv_make_fold(&L->conv_bn[i], nullptr), PVCONV_ACT_LEAKY,
-                              L->conv_slope, bf, dst, bf, w.conv_ws[i], s, /*packed=*/bf,
-                              w.split, i == 0 && sparse ? w.counts : nullptr,
-                              last && bf && (i > 0 || sparse) ? w.counts : nullptr);
+        const PvBnFold fold = pv_make_fold(&L->conv_bn[i], nullptr);
+        if (rows && (L->n_convs <= 2 || last)) {
+            PvConvRows c{};
+            c.x = src;
+            c.packed = w.conv_ws[i];
+            c.y = dst;
+            c.B = B;
+            c.R = R;
+            c.Cin = cin;
+            c.Cout = L->cout;
+            if (i == 1 && last) {
+                c.d1 = w.d1;
+                c.bn_in = pv_make_fold(&L->conv_bn[0], nullptr);
+            } else {
+                c.occ = w.counts;
+                c.occ_dense = i > 0;
+                c.d1_out = last ? nullptr : w.d1;
+            }
+            st = pv_launch_conv3d_rows(c, fold, PVCONV_ACT_LEAKY, L->conv_slope, s);
+        } else {
+            st = pv_launch_conv3d(src, B, R, cin, L->cout, L->conv_w[i], fold, PVCONV_ACT_LEAKY,
+                                  L->conv_slope, bf, dst, bf, w.conv_ws[i], s, /*packed=*/bf,
+                                  w.split, i == 0 && sparse ? w.counts : nullptr);
+        }
         if (st != PVCONV_OK) return st;
         void* t = src;
         src = dst;

@@ -115,38 +115,30 @@ __device__ __forceinline__ uint4 bload8_elems(__amdgpu_buffer_rsrc_t r, int voff
 // that started at +0, so it is skipped (same bits). A bitmap of the halo's
 // occupied voxels (one word per halo row) gives each wave, once per brick,
 // which of its blocks have an occupied input voxel at each tap.
-// OS (with need, the forward's last convolution, whose grid the
-// devoxelisation samples only at its points' trilinear corners, all within
-// one voxel of an occupied voxel): only the blocks of 32 output voxels with
-// an occupied voxel within one voxel run their MFMAs, dealt evenly to the
-// waves; a wave with none skips its fragment reads too, and a workgroup with
-// none returns before loading anything; the outputs they leave are not needed (their values are
-// unspecified, those of needed voxels the same bits as the full loop's).
 // Split-K (ksplit > 1): the input channels' chunks are divided among ksplit
 // groups of workgroups (cps chunks each); split s reads channels from
 // s*cps*16 (rows of x_ld elements), and writes its fp32 partial sums, without
 // batch norm or activation, to y + s*B*R^3*Cout (the caller passes an
 // identity fold and no activation); pv_conv_split_reduce_kernel adds them.
-template <int NB, int WCH, bool VEC, bool SB = false, bool SP = false, bool OS = false>
+template <int NB, int WCH, bool VEC, bool SB = false, bool SP = false>
 __global__ __launch_bounds__(256 * WCH, SB ? 2 : 1) void pv_conv3d_bf16_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ wpk, PvBnFold bn, int act,
     float slope, void* __restrict__ y, int out_bf16, int vec_out, int R, int Cin, int Cout,
-    int nbr, int nblocks, int x_ld, int ksplit, int cps, int B, const int32_t* __restrict__ occ,
-    const int32_t* __restrict__ need) {
+    int nbr, int nblocks, int x_ld, int ksplit, int cps, int B, const int32_t* __restrict__ occ) {
     __shared__ __attribute__((aligned(16))) char lds[SB ? kLdsBytesSB : kLdsBytes];
     __shared__ float bn_tab[2][NB * 32];  // folded scale and shift per output channel
-    // SP, OS: occupied w of each halo row
-    __shared__ uint32_t occ_row[SP || OS ? kHalo * kHalo : 1];
+    // SP: occupied w of each halo row
+    __shared__ uint32_t occ_row[SP ? kHalo * kHalo : 1];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // Blocks are dispatched round-robin over the 8 XCDs; give each XCD a
     // contiguous range of bricks so that neighbouring halos share its L2.
-    // With SP or OS a brick's work depends on its cloud's occupancy: there
+    // With SP a brick's work depends on its cloud's occupancy: there
     // each XCD takes an eighth of every cloud (whole clouds per XCD left the
     // XCDs that drew the denser clouds running long after the others).
     int bid = blockIdx.x;
     const int per = nblocks / max(B, 1);  // workgroups per cloud
-    if ((SP || OS) && (per & 7) == 0 && per * B == nblocks) {
+    if (SP && (per & 7) == 0 && per * B == nblocks) {
         // every XCD takes one contiguous eighth of every cloud, rotated by
         // the cloud, so that clouds of different occupancy share the XCDs
         const int x = bid & 7, k = bid >> 3, c = k / (per >> 3), j = k % (per >> 3);
@@ -190,19 +182,9 @@ __global__ __launch_bounds__(256 * WCH, SB ? 2 : 1) void pv_conv3d_bf16_kernel(
     // SB: one base per w shift of the taps (the half swap depends on w).
     constexpr int RP = SB ? kRowPitchSB : kRowPitch, HB = SB ? kHaloBytesSB : kHaloBytes;
     auto half_off = [](int hw, int h) { return SB ? (h ^ ((hw >> 2) & 1)) * 16 : h * 16; };
-    // Slot mb of the wave computes the block at u-slice blk_u(mb), v rows
-    // blk_v(mb)*4 .. +3: 2*wave + mb/2 and mb&1, unless OS deals the blocks
-    // out (then slot mb holds block g = bits 4mb .. 4mb+3 of gpack, u-slice
-    // g/2, v half g&1).
-    uint32_t gpack = 0u;
-    auto blk_u = [&](int mb) -> int {
-        if constexpr (OS) return (int)((gpack >> (4 * mb + 1)) & 7u);
-        return 2 * wv + (mb >> 1);
-    };
-    auto blk_v = [&](int mb) -> int {
-        if constexpr (OS) return (int)((gpack >> (4 * mb)) & 1u);
-        return mb & 1;
-    };
+    // Block mb of the wave: u-slice blk_u(mb), v rows blk_v(mb)*4 .. +3.
+    auto blk_u = [&](int mb) -> int { return 2 * wv + (mb >> 1); };
+    auto blk_v = [&](int mb) -> int { return mb & 1; };
     int bbase[4], bsw[4][3];
     auto place = [&](int mb, int ul, int vh) {
         const int vl = vh * 4 + (r32 >> 3), wl = r32 & 7;
@@ -213,7 +195,7 @@ __global__ __launch_bounds__(256 * WCH, SB ? 2 : 1) void pv_conv3d_bf16_kernel(
                           half_off(wl + tw, khalf);
     };
 #pragma unroll
-    for (int mb = 0; mb < 4; mb++) place(mb, 2 * wv + (mb >> 1), mb & 1);
+    for (int mb = 0; mb < 4; mb++) place(mb, blk_u(mb), blk_v(mb));
     // LDS byte address (in buffer 0) of block mb's B fragment at tap tn
     auto frag_addr = [&](int mb, int tn) {
         const int tu = tn / 9, tv = (tn / 3) % 3, tw = tn % 3;
@@ -234,7 +216,7 @@ __global__ __launch_bounds__(256 * WCH, SB ? 2 : 1) void pv_conv3d_bf16_kernel(
         x + cloud * x_ld + ulo * slab, (uint32_t)(((uhi - ulo) * slab - (x_ld - Cin)) * 2));
     const int pq = tid & 1;
     int goff[kSets], loff[kSets];
-    if constexpr (SP || OS) {
+    if constexpr (SP) {
         if (tid < kHalo * kHalo) occ_row[tid] = 0u;
         __syncthreads();
     }
@@ -249,9 +231,6 @@ __global__ __launch_bounds__(256 * WCH, SB ? 2 : 1) void pv_conv3d_bf16_kernel(
         if (occ && in) in = occ[cloud + ((size_t)gu * R + gv) * R + gw] > 0;
         if constexpr (SP)
             if (in && pq == 0) atomicOr(&occ_row[hu * kHalo + hv], 1u << hw);
-        if constexpr (OS && !SP)
-            if (in && pq == 0 && need[cloud + ((size_t)gu * R + gv) * R + gw] > 0)
-                atomicOr(&occ_row[hu * kHalo + hv], 1u << hw);
         goff[set] = in ? ((((gu - ulo) * R + gv) * R + gw) * x_ld + pq * 8) * 2 : kOOB;
         loff[set] = SB ? (hu * kHalo + hv) * kRowPitchSB + hw * kVoxPitchSB + half_off(hw, pq)
                        : (hu * kHalo + hv) * kRowPitch + hw * kVoxPitch + pq * 16;
@@ -301,47 +280,6 @@ __global__ __launch_bounds__(256 * WCH, SB ? 2 : 1) void pv_conv3d_bf16_kernel(
 #pragma unroll
         for (int set = 0; set < kSets; set++) any |= goff[set] != kOOB;
         live = __syncthreads_or(any);
-    }
-    // OS: block g's outputs (u-slice g/2, v rows (g&1)*4 .. +3) and their
-    // neighbours are halo rows g/2 .. +2 by (g&1)*4 .. +5, all ten w; the
-    // block is live when one of them holds an occupied voxel. A brick with no
-    // live block has nothing to compute or store. The live blocks are dealt
-    // to the waves in turn (slot k of wave w takes the (4k + w)-th), so that
-    // the brick's busiest wave has ceil(live / 4) of them; bit k of blive
-    // marks a slot that holds one.
-    bool wave_live = true;
-    uint32_t blive = 15u;
-    if constexpr (OS) {
-        if constexpr (!SP) __syncthreads();  // the bitmap is complete
-        bool lv = false;
-        if (lane < 16) {  // lane g tests block g
-            uint32_t m = 0u;
-#pragma unroll
-            for (int du = 0; du < 3; du++)
-#pragma unroll
-                for (int dv = 0; dv < 6; dv++)
-                    m |= occ_row[((lane >> 1) + du) * kHalo + (lane & 1) * 4 + dv];
-            lv = m != 0u;
-        }
-        const uint32_t bl = (uint32_t)__builtin_amdgcn_ballot_w64(lv);
-        if (bl == 0u) return;  // every wave reads the same bitmap
-        uint32_t m = bl;
-        const int ws = __builtin_amdgcn_readfirstlane(wv);
-        for (int i = 0; i < ws; i++) m &= m - 1u;
-        uint32_t gp = 0u, bv = 0u;
-#pragma unroll
-        for (int k = 0; k < 4; k++) {
-            const uint32_t g = m ? (uint32_t)__builtin_ctz(m) : 0u;  // idle: valid addresses
-            bv |= (m ? 1u : 0u) << k;
-            gp |= g << (4 * k);
-#pragma unroll
-            for (int i = 0; i < 4; i++) m &= m - 1u;  // past the next four live blocks
-        }
-        gpack = __builtin_amdgcn_readfirstlane(gp);
-        blive = __builtin_amdgcn_readfirstlane(bv);
-#pragma unroll
-        for (int k = 0; k < 4; k++) place(k, blk_u(k), blk_v(k));
-        wave_live = blive != 0u;
     }
     // SP: bit 10*tv + w of msk[mb][tu] is set when block mb's input row
     // (tu, tv) holds an occupied voxel at halo w; the block's fragment at tap
@@ -415,18 +353,13 @@ __global__ __launch_bounds__(256 * WCH, SB ? 2 : 1) void pv_conv3d_bf16_kernel(
                 if (fetch && t >= kHaloLag && t < kSets + kHaloLag)
                     *(uint4*)(lds + loff[t - kHaloLag] + nxt_off) = hr[(t - kHaloLag) % kHaloLag];
                 if (fetch && t < kSets) hr[t % kHaloLag] = halo_load(t, cn);
-                if (t + 1 < kTaps && (!OS || wave_live)) {
+                if (t + 1 < kTaps) {
 #pragma unroll
                     for (int mb = 0; mb < 4; mb++)
                         bf[nxt][mb] = *(const pv_bf16x8*)(lds + frag_addr(mb, t + 1) + cur_off);
                 }
 #pragma unroll
-                for (int mb = 0; mb < 4 && (!OS || wave_live); mb++) {
-                    if constexpr (OS) {
-                        uint32_t bb = blive;
-                        asm volatile("" : "+s"(bb));
-                        if (((bb >> mb) & 1u) == 0u) continue;
-                    }
+                for (int mb = 0; mb < 4; mb++) {
                     if constexpr (SP) {
                         // opaque here, so that the test stays a scalar shift,
                         // mask and branch inside the loop (hoisted, the 108
@@ -479,7 +412,6 @@ __global__ __launch_bounds__(256 * WCH, SB ? 2 : 1) void pv_conv3d_bf16_kernel(
                     const int cb = (nl - pass * PW) * esz;  // byte offset in the row
 #pragma unroll
                     for (int mb = 0; mb < 4; mb++) {
-                        if (OS && ((blive >> mb) & 1u) == 0u) continue;  // an idle slot
                         const int vox = blk_u(mb) * 64 + (blk_v(mb) * 4 + (r32 >> 3)) * 8 +
                                         (r32 & 7);
                         float r[4] = {acc[mb][nb][4 * j + 0] * sc.x + sh.x,
@@ -558,6 +490,362 @@ __global__ __launch_bounds__(256 * WCH, SB ? 2 : 1) void pv_conv3d_bf16_kernel(
         epilogue(std::integral_constant<bool, true>{});
     else
         epilogue(std::integral_constant<bool, false>{});
+}
+
+// ---------------------------------------------------------------------------
+// The convolutions inside a layer's forward compute only the rows (voxels)
+// that matter. Their grids are internal: the first one's input is zero but for
+// the occupied voxels, and the last one's output is read by the devoxelisation
+// alone, at its points' corner cells, all within one voxel of an occupied
+// voxel. D1, the voxels within one voxel of an occupied one, is therefore
+// everything the last convolution has to compute (18 % of a part-segmentation
+// grid at R = 32, 37-40 % at R = 16), and everything in which the first one's
+// output differs from the constant act(BN(0)) that an empty neighbourhood
+// gives.
+//
+// A workgroup owns an 8x8x8 brick and 32*NB channels, as the dense kernel does,
+// but gathers the brick's D1 voxels into a list and multiplies blocks of 32 of
+// them: a fragment read names a voxel per lane, so any 32 voxels of the brick
+// make a block. What bounded the brick with aligned blocks was not the MFMAs
+// but what each wave loads per tap: its weights, 1 KB per 32 channels, whatever
+// the number of its voxels (64 channels a wave: 55 k cycles of the vector
+// cache against 27 k of MFMAs per live brick). Here the waves are WC channel
+// groups x 4/WC voxel groups, each with all its share of the blocks (S at
+// most) and few channels: weights and fragment reads then cost less than the
+// MFMAs.
+//
+// The halo is compact: 32 bytes a voxel, 336 a row of ten, so that voxel
+// (u, v, w) starts in 16-byte bank 2w + 2u + 5v (mod 16) plus a constant, under
+// every tap. Sixteen lanes are served together: the list deals the voxels so
+// that position p holds a voxel of bank class p mod 16 as far as the classes
+// reach, and the reads do not conflict.
+//
+// Input modes: occ, a sparse grid (voxels of count 0 read as zero; their rows
+// may be unwritten); with occ_dense, a whole grid of which occ gives only the
+// points' voxels; CB: the output of such a convolution, whose rows exist in D1
+// (bits d1, one byte per eight w) and are elsewhere the constant of its batch
+// norm bn_in, which the halo takes from a table.
+// d1_out: the convolution writes its D1 bits for the next one.
+// Outputs outside D1 are not written.
+// ---------------------------------------------------------------------------
+constexpr int kRowsRow = kHalo * 32 + 16;              // 336
+constexpr int kRowsHalo = kHalo * kHalo * kRowsRow;    // 33600 per buffer
+constexpr int kRowsMaxCin = 256;                       // CB: the constant's table
+
+template <int NB, int WC, int S, bool VEC, bool CB>
+__global__ __launch_bounds__(256, 2) void pv_conv3d_rows_kernel(
+    const uint16_t* __restrict__ x, const uint16_t* __restrict__ wpk, PvBnFold bn,
+    PvBnFold bn_in, float neg, uint16_t* __restrict__ y, int R, int Cin, int Cout, int nbr,
+    int nblocks, int B, const int32_t* __restrict__ occ, int occ_dense,
+    const uint8_t* __restrict__ d1, uint8_t* __restrict__ d1_out) {
+    constexpr int NBW = NB / WC, VG = 4 / WC, NT = NB * 32;
+    static_assert(NB % WC == 0 && VG * S >= 16, "the waves hold every block of the brick");
+    __shared__ __attribute__((aligned(16))) char lds[2 * kRowsHalo];
+    __shared__ __attribute__((aligned(16))) uint16_t s_const[CB ? kRowsMaxCin : 8];
+    __shared__ __attribute__((aligned(16))) float bn_tab[2][NT];
+    __shared__ uint32_t s_bits[kHalo * kHalo];  // halo rows: occupied, or (CB) D1
+    __shared__ __attribute__((aligned(16))) int s_cls[16];
+    __shared__ uint16_t s_row[512];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wg = wave / WC, wc = wave % WC;
+    // every XCD takes one contiguous eighth of every cloud, rotated by the
+    // cloud: a brick's work follows its cloud's occupancy
+    int bid = blockIdx.x;
+    const int per = nblocks / B;
+    if ((per & 7) == 0) {
+        const int xcd = bid & 7, k = bid >> 3, c = k / (per >> 3), j = k % (per >> 3);
+        bid = c * per + ((xcd + c) & 7) * (per >> 3) + j;
+    } else if ((nblocks & 7) == 0) {
+        bid = (bid & 7) * (nblocks >> 3) + (bid >> 3);
+    }
+    const int ntiles = (Cout + NT - 1) / NT;
+    const int nt = bid % ntiles;
+    bid /= ntiles;
+    const int bw = bid % nbr;
+    bid /= nbr;
+    const int bv = bid % nbr;
+    bid /= nbr;
+    const int bu = bid % nbr;
+    const int b = bid / nbr;
+    const int u0 = bu * kBrick, v0 = bv * kBrick, w0 = bw * kBrick, n0 = nt * NT;
+    const size_t cloud = (size_t)b * R * R * R;
+    const int nch = (Cin + kKC - 1) / kKC;
+
+    // --- the halo's bits
+    if (tid < 16) s_cls[tid] = 0;
+    ((uint32_t*)s_row)[tid] = 0xffffffffu;  // no voxel
+    if constexpr (CB) {
+        if (tid < kHalo * kHalo) {
+            const int gu = u0 + tid / kHalo - 1, gv = v0 + tid % kHalo - 1;
+            uint32_t m = 0u;
+            if (gu >= 0 && gu < R && gv >= 0 && gv < R) {
+                const uint8_t* p = d1 + (((size_t)b * R + gu) * R + gv) * nbr + bw;
+                m = (uint32_t)p[0] << 1;
+                if (bw > 0) m |= p[-1] >> 7;
+                if (bw + 1 < nbr) m |= (uint32_t)(p[1] & 1u) << 9;
+            }
+            s_bits[tid] = m;
+        }
+        for (int c = tid; c < Cin; c += 256) {
+            float sc, sh;
+            pv_bn_coeffs(bn_in, c, sc, sh);
+            const float r = 0.f * sc + sh;
+            s_const[c] = pv_f32_to_bf16(r >= 0.f ? r : r * neg);
+        }
+    } else {
+        int n[4];
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const int h = tid + i * 256;
+            const int gu = u0 + h / (kHalo * kHalo) - 1, gv = v0 + (h / kHalo) % kHalo - 1,
+                      gw = w0 + h % kHalo - 1;
+            n[i] = 0;
+            if (h < kHaloVox && gu >= 0 && gu < R && gv >= 0 && gv < R && gw >= 0 && gw < R)
+                n[i] = occ[cloud + ((size_t)gu * R + gv) * R + gw];
+        }
+        if (tid < kHalo * kHalo) s_bits[tid] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const int h = tid + i * 256;
+            if (n[i] > 0) atomicOr(&s_bits[h / kHalo], 1u << (h % kHalo));
+        }
+    }
+    __syncthreads();
+
+    // --- the list of the brick's D1 voxels: thread tid takes two of row
+    // (ru, rv). Their order within a bank class is that of the atomics and
+    // does not matter: each output's arithmetic is its own.
+    const int ru = tid >> 5, rv = (tid >> 2) & 7, rw = (tid & 3) * 2;
+    uint32_t need;
+    if constexpr (CB) {
+        need = s_bits[(ru + 1) * kHalo + rv + 1] >> 1;
+    } else {
+        uint32_t m = 0u;
+#pragma unroll
+        for (int du = 0; du < 3; du++)
+#pragma unroll
+            for (int dv = 0; dv < 3; dv++) m |= s_bits[(ru + du) * kHalo + rv + dv];
+        need = m | (m >> 1) | (m >> 2);
+    }
+    const bool in_row = u0 + ru < R && v0 + rv < R;
+    need &= in_row ? (w0 + kBrick <= R ? 0xffu : (1u << (R - w0)) - 1u) : 0u;
+    if (!CB && d1_out && nt == 0 && in_row && (tid & 3) == 0)
+        d1_out[(((size_t)b * R + u0 + ru) * R + v0 + rv) * nbr + bw] = (uint8_t)need;
+    int rank[2], cls[2];
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+        cls[i] = (2 * (rw + i) + 2 * ru + 5 * rv) & 15;
+        rank[i] = (need >> (rw + i)) & 1u ? atomicAdd(&s_cls[cls[i]], 1) : -1;
+    }
+    __syncthreads();
+    int total = 0;
+#pragma unroll
+    for (int c = 0; c < 16; c++) total += s_cls[c];
+    total = __builtin_amdgcn_readfirstlane(total);
+    if (total == 0) return;  // uniform: nothing near a point in this brick
+    const int P = (total + 15) >> 4;  // groups of sixteen
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+        if (rank[i] < 0) continue;
+        int pos = rank[i] * 16 + cls[i];
+        if (rank[i] >= P) {
+            // past the class's share: the places other classes leave, in order
+            int e = rank[i] - P;
+            for (int c = 0; c < cls[i]; c++) e += max(s_cls[c] - P, 0);
+            int c = 0;
+            while (c < 15 && e >= max(P - s_cls[c], 0)) e -= max(P - s_cls[c++], 0);
+            pos = (s_cls[c] + e) * 16 + c;
+        }
+        s_row[pos] = (uint16_t)(ru * 64 + rv * 8 + rw + i);
+    }
+
+    // --- halo pieces of this thread: piece p = set*256 + tid is voxel p/2,
+    // channels (p%2)*8 .. +7 of the chunk
+    constexpr int kSets = (kPieces + 255) / 256;
+    const int ulo = max(u0 - 1, 0), uhi = min(u0 + kBrick + 1, R);
+    const size_t slab = (size_t)R * R * Cin;
+    const __amdgpu_buffer_rsrc_t xr =
+        make_rsrc(x + cloud * Cin + ulo * slab, (uint32_t)((uhi - ulo) * slab * 2));
+    const int pq = tid & 1;
+    int goff[kSets], loff[kSets];
+    uint32_t konst = 0u;  // CB: the sets that take the constant
+#pragma unroll
+    for (int set = 0; set < kSets; set++) {
+        const int h = min(set * 128 + (tid >> 1), kHaloVox - 1);
+        const int hr = h / kHalo, hu = hr / kHalo, hv = hr % kHalo, hw = h % kHalo;
+        const int gu = u0 + hu - 1, gv = v0 + hv - 1, gw = w0 + hw - 1;
+        const bool grid = gu >= 0 && gu < R && gv >= 0 && gv < R && gw >= 0 && gw < R;
+        const bool bit = (s_bits[hr] >> hw) & 1u;
+        const bool in = grid && (bit || (!CB && occ_dense));
+        if (CB && grid && !bit) konst |= 1u << set;
+        goff[set] = in ? ((((gu - ulo) * R + gv) * R + gw) * Cin + pq * 8) * 2 : kOOB;
+        loff[set] = hr * kRowsRow + hw * 32 + pq * 16;
+    }
+    auto halo_load = [&](int set, int cc) -> uint4 {
+        if (VEC) return bload16(xr, cc + pq * 8 < Cin ? goff[set] : kOOB, cc * 2);
+        return bload8_elems(xr, goff[set], cc * 2, Cin - cc - pq * 8);
+    };
+    auto halo_store = [&](int set, int off, uint4 v, uint4 kv) {
+        if constexpr (CB) {
+            const bool k = (konst >> set) & 1u;
+            v.x = k ? kv.x : v.x;
+            v.y = k ? kv.y : v.y;
+            v.z = k ? kv.z : v.z;
+            v.w = k ? kv.w : v.w;
+        }
+        *(uint4*)(lds + off + loff[set]) = v;
+    };
+    auto const_of = [&](int cc) -> uint4 {
+        if constexpr (CB)
+            if (cc + pq * 8 < Cin) return *(const uint4*)&s_const[cc + pq * 8];
+        return make_uint4(0u, 0u, 0u, 0u);
+    };
+
+    const int G = (Cout + 31) / 32;
+    const __amdgpu_buffer_rsrc_t wr = make_rsrc(wpk, (uint32_t)((size_t)nch * kTaps * G * 1024));
+    const int wlane = lane * 16;
+    auto load_w = [&](int c, int tap, pv_bf16x8 (&wf)[NBW]) {
+        const int cc = c < nch ? c : nch - 1;  // past the end: reload, never used
+#pragma unroll
+        for (int nb = 0; nb < NBW; nb++)
+            wf[nb] = as_frag(bload16(wr, wlane,
+                                     ((cc * kTaps + tap) * G + nt * NB + wc * NBW + nb) * 1024));
+    };
+    if (tid < NT) {  // channels past Cout take the last one's (never stored)
+        float sc, sh;
+        pv_bn_coeffs(bn, min(n0 + tid, Cout - 1), sc, sh);
+        bn_tab[0][tid] = sc;
+        bn_tab[1][tid] = sh;
+    }
+    {
+        const uint4 kv = const_of(0);
+#pragma unroll
+        for (int set = 0; set < kSets; set++) halo_store(set, 0, halo_load(set, 0), kv);
+    }
+    __syncthreads();
+
+    // --- n blocks of this wave: block k*VG + wg of the list in slot k
+    const int r32 = lane & 31, khalf = lane >> 5;
+    const int blocks = (P + 1) >> 1;
+    auto run = [&](auto count) {
+        constexpr int n = decltype(count)::value;
+        constexpr int kWD = n > 4 ? 2 : 8, kWR = kWD + 1, kHaloLag = 4;
+        static_assert(kTaps % kWR == 0, "the weight ring realigns at every chunk");
+        constexpr int nr = n > 0 ? n : 1;
+        int base[nr];
+#pragma unroll
+        for (int k = 0; k < n; k++) {
+            const int vox = s_row[(k * VG + wg) * 32 + r32] & 511;  // none: any voxel
+            base[k] = ((vox >> 6) * kHalo + ((vox >> 3) & 7)) * kRowsRow + (vox & 7) * 32 +
+                      khalf * 16;
+        }
+        pv_f32x16 acc[nr][NBW];
+#pragma unroll
+        for (int i = 0; i < n; i++)
+#pragma unroll
+            for (int j = 0; j < NBW; j++)
+#pragma unroll
+                for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
+        pv_bf16x8 wf[kWR][NBW];
+        if (n > 0) {
+#pragma unroll
+            for (int k = 0; k < kWD; k++) load_w(0, k, wf[k]);
+        }
+        for (int c = 0; c < nch; c++) {
+            const int cur_off = (c & 1) * kRowsHalo, nxt_off = kRowsHalo - cur_off;
+            // past the last chunk the next halo loads out of range (zeros):
+            // unconditional loads keep the wait counts exact. Element-wise
+            // loads (!VEC: few input channels) follow the taps instead, for
+            // their registers.
+            const int cn = c + 1 < nch ? (c + 1) * kKC : Cin;
+            const uint4 kv = const_of(cn);
+            pv_bf16x8 bf[2][nr];
+            uint4 hr[kHaloLag];
+#pragma unroll
+            for (int k = 0; k < n; k++)
+                bf[0][k] = *(const pv_bf16x8*)(lds + base[k] + cur_off);
+#pragma unroll
+            for (int t = 0; t < kTaps; t++) {
+                if (n > 0) {
+                    if (t + kWD < kTaps)
+                        load_w(c, t + kWD, wf[(t + kWD) % kWR]);
+                    else
+                        load_w(c + 1, t + kWD - kTaps, wf[(t + kWD) % kWR]);
+                }
+                if (VEC && t >= kHaloLag && t < kSets + kHaloLag)
+                    halo_store(t - kHaloLag, nxt_off, hr[(t - kHaloLag) % kHaloLag], kv);
+                if (VEC && t < kSets) hr[t % kHaloLag] = halo_load(t, cn);
+                if (t + 1 < kTaps) {
+                    const int tn = t + 1;
+                    const int off = ((tn / 9) * kHalo + (tn / 3) % 3) * kRowsRow + (tn % 3) * 32;
+#pragma unroll
+                    for (int k = 0; k < n; k++)
+                        bf[tn & 1][k] = *(const pv_bf16x8*)(lds + base[k] + off + cur_off);
+                }
+#pragma unroll
+                for (int k = 0; k < n; k++)
+#pragma unroll
+                    for (int nb = 0; nb < NBW; nb++)
+                        acc[k][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            wf[t % kWR][nb], bf[t & 1][k], acc[k][nb], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (!VEC && c + 1 < nch) {
+#pragma unroll 1
+                for (int p = tid; p < kPieces; p += 256) {
+                    const int h = p >> 1, h_r = h / kHalo, hw = h % kHalo;
+                    const int gu = u0 + h_r / kHalo - 1, gv = v0 + h_r % kHalo - 1,
+                              gw = w0 + hw - 1;
+                    const bool in = gu >= 0 && gu < R && gv >= 0 && gv < R && gw >= 0 && gw < R &&
+                                    (occ_dense || ((s_bits[h_r] >> hw) & 1u));
+                    *(uint4*)(lds + nxt_off + h_r * kRowsRow + hw * 32 + pq * 16) = bload8_elems(
+                        xr, in ? ((((gu - ulo) * R + gv) * R + gw) * Cin + pq * 8) * 2 : kOOB,
+                        cn * 2, Cin - cn - pq * 8);
+                }
+            }
+            pv_lds_barrier();  // LDS only: the weight prefetch stays in flight
+        }
+        // lane l holds voxel l % 32 of a block and channels 8j + 4 (l / 32) + i
+#pragma unroll
+        for (int k = 0; k < n; k++) {
+            const int vox = s_row[(k * VG + wg) * 32 + r32];
+            if (vox >= 512) continue;
+            uint16_t* row = y + (cloud + ((size_t)(u0 + (vox >> 6)) * R + v0 + ((vox >> 3) & 7)) * R +
+                                 w0 + (vox & 7)) * Cout;
+#pragma unroll
+            for (int nb = 0; nb < NBW; nb++)
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    const int nl = (wc * NBW + nb) * 32 + 8 * j + 4 * khalf;
+                    if (n0 + nl >= Cout) continue;
+                    const float4 sc = *(const float4*)&bn_tab[0][nl];
+                    const float4 sh = *(const float4*)&bn_tab[1][nl];
+                    float r[4] = {acc[k][nb][4 * j + 0] * sc.x + sh.x,
+                                  acc[k][nb][4 * j + 1] * sc.y + sh.y,
+                                  acc[k][nb][4 * j + 2] * sc.z + sh.z,
+                                  acc[k][nb][4 * j + 3] * sc.w + sh.w};
+#pragma unroll
+                    for (int e = 0; e < 4; e++) r[e] = r[e] >= 0.f ? r[e] : r[e] * neg;
+                    *(uint2*)(row + n0 + nl) =
+                        make_uint2(pv_pack_bf16x2(r[0], r[1]), pv_pack_bf16x2(r[2], r[3]));
+                }
+        }
+    };
+    const int mine = __builtin_amdgcn_readfirstlane((blocks - wg + VG - 1) / VG);
+    switch (mine) {  // one straight loop for each number of blocks
+        case 0: run(std::integral_constant<int, 0>{}); break;
+        case 1: run(std::integral_constant<int, 1>{}); break;
+        case 2: run(std::integral_constant<int, 2>{}); break;
+        case 3: run(std::integral_constant<int, 3>{}); break;
+        case 4: run(std::integral_constant<int, 4>{}); break;
+        default:
+            if constexpr (S > 4) {
+                if (mine <= 6) run(std::integral_constant<int, 6>{});
+                else run(std::integral_constant<int, 8>{});
+            }
+    }
 }
 
 // Repack bf16 weights [Cout][27][Cin] into the fragment order the MFMA conv
@@ -678,33 +966,43 @@ __global__ __launch_bounds__(256) void pv_conv_split_reduce_kernel(
 template <int NB, int WCH, bool SB = false>
 void launch_bf16(const void* x, int B, int R, int Cin, int Cout, const void* w,
                  const PvBnFold& bn, int act, float slope, void* y, bool out_bf16, bool vec,
-                 hipStream_t s, int ksplit = 1, int cps = 0, const int32_t* occ = nullptr,
-                 const int32_t* need = nullptr) {
+                 hipStream_t s, int ksplit = 1, int cps = 0, const int32_t* occ = nullptr) {
     const int nbr = (R + kBrick - 1) / kBrick;
     const size_t blocks =
         (size_t)B * nbr * nbr * nbr * ((Cout + NB * 32 - 1) / (NB * 32)) * ksplit;
     // 16-byte stores: aligned output with rows of whole 16-byte pieces
     const bool vec_out = pv_aligned16(y) && ((size_t)Cout * (out_bf16 ? 2 : 4)) % 16 == 0;
-#define PV_CONV(V, SPX, OSX)                                                                \
-    hipLaunchKernelGGL((pv_conv3d_bf16_kernel<NB, WCH, V, SB, SPX, OSX>),                   \
-                       dim3((unsigned)blocks),                                                 \
+#define PV_CONV(V, SPX)                                                                     \
+    hipLaunchKernelGGL((pv_conv3d_bf16_kernel<NB, WCH, V, SB, SPX>), dim3((unsigned)blocks),   \
                        dim3(256 * WCH), 0, s, (const uint16_t*)x, (const uint16_t*)w, bn, act, \
                        slope, y, (int)out_bf16, (int)vec_out, R, Cin, Cout, nbr, (int)blocks, \
-                       Cin, ksplit, cps, B, occ, need)
-    // a sparse input on the two-per-CU form skips its empty fragments' MFMAs,
-    // a needed-output mask its unneeded blocks, waves and bricks (given
-    // together, the two are the same counts)
-    if (vec && SB && occ && need)
-        PV_CONV(true, SB, SB);
-    else if (vec && SB && occ)
-        PV_CONV(true, SB, false);
-    else if (vec && SB && need)
-        PV_CONV(true, false, SB);
+                       Cin, ksplit, cps, B, occ)
+    // a sparse input on the two-per-CU form skips its empty fragments' MFMAs
+    if (vec && SB && occ)
+        PV_CONV(true, SB);
     else if (vec)
-        PV_CONV(true, false, false);
+        PV_CONV(true, false);
     else
-        PV_CONV(false, false, false);
+        PV_CONV(false, false);
 #undef PV_CONV
+}
+
+template <int NB, int WC, int S>
+void launch_rows(const PvConvRows& c, const PvBnFold& bn, float neg, bool vec, hipStream_t s) {
+    const int nbr = (c.R + kBrick - 1) / kBrick;
+    const int blocks = c.B * nbr * nbr * nbr * ((c.Cout + NB * 32 - 1) / (NB * 32));
+#define PV_ROWS_CONV(V, CBX)                                                                  \
+    hipLaunchKernelGGL((pv_conv3d_rows_kernel<NB, WC, S, V, CBX>), dim3(blocks), dim3(256), 0, s, \
+                       (const uint16_t*)c.x, (const uint16_t*)c.packed, bn, c.bn_in, neg,       \
+                       (uint16_t*)c.y, c.R, c.Cin, c.Cout, nbr, blocks, c.B, c.occ,             \
+                       (int)c.occ_dense, c.d1, c.d1_out)
+    if (c.d1)
+        PV_ROWS_CONV(true, true);
+    else if (vec)
+        PV_ROWS_CONV(true, false);
+    else
+        PV_ROWS_CONV(false, false);
+#undef PV_ROWS_CONV
 }
 
 }  // namespace
@@ -758,7 +1056,7 @@ size_t pv_conv3d_split_ws_bytes(int B, int R, int Cin, int Cout) {
 pvconv_status pv_launch_conv3d(const void* x, int B, int R, int Cin, int Cout, const void* w,
                                const PvBnFold& bn, int act, float slope, bool bf16, void* y,
                                bool out_bf16, void* ws, hipStream_t s, bool packed,
-                               float* split_ws, const int32_t* occ, const int32_t* need) {
+                               float* split_ws, const int32_t* occ) {
     if (B == 0) return PVCONV_OK;
     if (bf16) {
         if (!packed) {
@@ -801,8 +1099,7 @@ pvconv_status pv_launch_conv3d(const void* x, int B, int R, int Cin, int Cout, c
         // accumulator registers and spill in its epilogue).
         const bool two = Cin <= 64;
         if (Cin <= 128 && Cout % 64 == 0 && bricks * (Cout / 64) >= 512) {
-            launch_bf16<2, 1, true>(x, B, R, Cin, Cout, w, bn, act, slope, y, out_bf16, vec, s, 1, 0, occ,
-                                    need);
+            launch_bf16<2, 1, true>(x, B, R, Cin, Cout, w, bn, act, slope, y, out_bf16, vec, s, 1, 0, occ);
         } else if (Cout % 64 == 0 && bricks * (Cout / 64) >= 256) {
             if (two)
                 launch_bf16<2, 2>(x, B, R, Cin, Cout, w, bn, act, slope, y, out_bf16, vec, s, 1, 0, occ);
@@ -823,5 +1120,29 @@ pvconv_status pv_launch_conv3d(const void* x, int B, int R, int Cin, int Cout, c
                                (const float*)x, (const float*)w, bn, act, slope, y, (int)out_bf16,
                                B, R, Cin, Cout);
     }
+    return pv_launch_status();
+}
+
+bool pv_conv3d_rows_ok(int B, int R, int Cin, int Cout, int n_convs) {
+    // grids so small that the dense convolution splits its input channels
+    // keep that form
+    return Cout % 8 == 0 && Cout <= kRowsMaxCin && pv_conv3d_splits(B, R, Cin, Cout) == 1 &&
+           (n_convs < 2 || pv_conv3d_splits(B, R, Cout, Cout) == 1);
+}
+
+size_t pv_conv3d_rows_d1_bytes(int B, int R) {
+    return (size_t)B * R * R * ((R + kBrick - 1) / kBrick);
+}
+
+pvconv_status pv_launch_conv3d_rows(const PvConvRows& c, const PvBnFold& bn, int act, float slope,
+                                    hipStream_t s) {
+    const float neg = act == PVCONV_ACT_LEAKY ? slope : (act == PVCONV_ACT_RELU ? 0.f : 1.f);
+    const bool vec = c.Cin % 8 == 0 && pv_aligned16(c.x);
+    const int nbr = (c.R + kBrick - 1) / kBrick;
+    const long bricks = (long)c.B * nbr * nbr * nbr;
+    if (c.Cout % 64 == 0 && bricks * (c.Cout / 64) >= 512)
+        launch_rows<2, 2, 8>(c, bn, neg, vec, s);
+    else
+        launch_rows<1, 1, 4>(c, bn, neg, vec, s);
     return pv_launch_status();
 }

@@ -172,16 +172,28 @@ __device__ __forceinline__ void pv_pack_role(const PvPackJobs& jobs, int blk,
 // small to fill the chip then split the input channels across workgroups
 // (fixed-order sum of the partials), else they run unsplit. occ: per-voxel
 // counts of the input grid [B][R^3] or nullptr; with it, input voxels of
-// count 0 read as zero and their rows are never read (a sparse grid). need:
-// per-voxel counts of the layer's points [B][R^3] or nullptr; with it only
-// the outputs within one voxel of an occupied voxel are computed (those a
-// devoxelisation of the points reads), the others left unspecified (where
-// given together, occ and need are the same counts).
+// count 0 read as zero and their rows are never read (a sparse grid).
 pvconv_status pv_launch_conv3d(const void* x, int B, int R, int Cin, int Cout, const void* w,
                                const PvBnFold& bn, int act, float slope, bool bf16, void* y,
                                bool out_bf16, void* ws, hipStream_t s, bool packed = false,
-                               float* split_ws = nullptr, const int32_t* occ = nullptr,
-                               const int32_t* need = nullptr);
+                               float* split_ws = nullptr, const int32_t* occ = nullptr);
+// A convolution inside a layer's forward that computes only D1, the voxels
+// within one voxel of an occupied one (bf16 grids, packed weights).
+struct PvConvRows {
+    const void* x;       // [B][R^3][Cin] bf16
+    const void* packed;  // pv_pack_job's weights
+    void* y;             // [B][R^3][Cout] bf16, written in D1 only
+    int B, R, Cin, Cout;
+    const int32_t* occ;  // the points' counts [B][R^3]; unless occ_dense, x is
+    bool occ_dense;      // zero (its rows unread) where they are 0
+    uint8_t* d1_out;     // or NULL: D1's bits, one byte per eight w
+    const uint8_t* d1;   // or NULL: x is the output of such a convolution with
+    PvBnFold bn_in;      // these bits, this batch norm and the same activation
+};
+bool pv_conv3d_rows_ok(int B, int R, int Cin, int Cout, int n_convs);
+size_t pv_conv3d_rows_d1_bytes(int B, int R);
+pvconv_status pv_launch_conv3d_rows(const PvConvRows& c, const PvBnFold& bn, int act, float slope,
+                                    hipStream_t s);
 int pv_conv3d_splits(int B, int R, int Cin, int Cout);
 size_t pv_conv3d_split_ws_bytes(int B, int R, int Cin, int Cout);
 pvconv_status pv_launch_devoxelize(const void* grid, int B, int R, int C, bool grid_bf16,
