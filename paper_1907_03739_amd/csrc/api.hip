@@ -58,7 +58,7 @@ struct ForwardWs {
     void* grid_a;
     void* grid_b;
     float* devox;
-    uint8_t* d1;   // bits of the voxels the convolutions compute
+    PvConvPlan plan;  // the voxels the convolutions compute
     float* split;  // fp32 partial sums of split convolutions (small grids), or NULL
     size_t total;
 };
@@ -86,7 +86,12 @@ ForwardWs carve_forward(void* base, int B, int N, const pvconv_layer* L) {
     w.grid_a = take((size_t)B * V * cmax * es);
     w.grid_b = take((size_t)B * V * L->cout * es);
     w.devox = (float*)take((size_t)B * N * L->cout * 4);
-    w.d1 = (uint8_t*)take(pv_conv3d_rows_d1_bytes(B, L->R));
+    w.plan = PvConvPlan{};
+    if (L->compute_dt == PVCONV_BF16) {
+        size_t plan_bytes = 0;
+        pv_conv_plan_carve(nullptr, B, L->R, &plan_bytes);
+        w.plan = pv_conv_plan_carve(take(plan_bytes), B, L->R, &plan_bytes);
+    }
     size_t split = 0;
     if (L->compute_dt == PVCONV_BF16)
         for (int i = 0; i < L->n_convs; i++) {
@@ -572,9 +577,12 @@ pvconv_status pvconv_forward_ex(const float* coords, const void* feats, pvconv_d
     // of the normalisation launch (or in a launch of their own when the
     // normalisation is skipped)
     PvPackJobs jobs{};
-    if (bf)
+    if (bf) {
+        jobs.zero = w.plan.count[0];
+        jobs.nzero = kPvPlanCounts;
         for (int i = 0; i < L->n_convs; i++)
             pv_pack_job(jobs, L->conv_w[i], i ? L->cout : L->cin, L->cout, w.conv_ws[i]);
+    }
     // bf16 small clouds: the grid holds only its occupied rows (most voxels
     // are empty: their rows are neither written nor read); the first
     // convolution reads the counts and takes empty voxels as zero
@@ -598,6 +606,11 @@ pvconv_status pvconv_forward_ex(const float* coords, const void* feats, pvconv_d
     // outputs are computed. With one or two convolutions the first one's
     // output is also computed only there, and constant elsewhere.
     const bool rows = bf && pv_conv3d_rows_ok(B, R, cin, L->cout, L->n_convs);
+    if (rows) {
+        st = pv_launch_conv_plan(w.plan, w.counts, pnorm, L->devox == PVCONV_DEVOX_NEAREST, B, N,
+                                 R, L->cout, s);
+        if (st != PVCONV_OK) return st;
+    }
     for (int i = 0; i < L->n_convs; i++) {
         const bool last = i == L->n_convs - 1;
         const PvBnFold fold = pv_make_fold(&L->conv_bn[i], nullptr);
@@ -610,14 +623,13 @@ pvconv_status pvconv_forward_ex(const float* coords, const void* feats, pvconv_d
             c.R = R;
             c.Cin = cin;
             c.Cout = L->cout;
-            if (i == 1 && last) {
-                c.d1 = w.d1;
+            c.plan = w.plan;
+            c.which = last ? 1 : 0;
+            c.counts = w.counts;
+            c.input = i == 0 ? PvConvRows::kOccupied
+                             : (i == 1 ? PvConvRows::kRowsOfFirst : PvConvRows::kWhole);
+            if (c.input == PvConvRows::kRowsOfFirst)
                 c.bn_in = pv_make_fold(&L->conv_bn[0], nullptr);
-            } else {
-                c.occ = w.counts;
-                c.occ_dense = i > 0;
-                c.d1_out = last ? nullptr : w.d1;
-            }
             st = pv_launch_conv3d_rows(c, fold, PVCONV_ACT_LEAKY, L->conv_slope, s);
         } else {
             st = pv_launch_conv3d(src, B, R, cin, L->cout, L->conv_w[i], fold, PVCONV_ACT_LEAKY,

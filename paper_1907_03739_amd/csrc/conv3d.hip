@@ -36,6 +36,7 @@
 #include <algorithm>
 
 #include "pv_common.h"
+#include "pv_trilinear.h"
 
 namespace {
 
@@ -497,169 +498,430 @@ __global__ __launch_bounds__(256 * WCH, SB ? 2 : 1) void pv_conv3d_bf16_kernel(
 // that matter. Their grids are internal: the first one's input is zero but for
 // the occupied voxels, and the last one's output is read by the devoxelisation
 // alone, at its points' corner cells, all within one voxel of an occupied
-// voxel. D1, the voxels within one voxel of an occupied one, is therefore
-// everything the last convolution has to compute (18 % of a part-segmentation
-// grid at R = 32, 37-40 % at R = 16), and everything in which the first one's
-// output differs from the constant act(BN(0)) that an empty neighbourhood
-// gives.
+// voxel. So the last convolution computes the voxels read, and a first one
+// before it D1, the voxels within one voxel of an occupied one: everywhere
+// else its output is the constant act(BN(0)) that an empty neighbourhood
+// gives. (Part-segmentation clouds at R = 32: 12 % and 18 % of the grid, at
+// R = 16 24 % and 38 %.)
 //
-// A workgroup owns an 8x8x8 brick and 32*NB channels, as the dense kernel does,
-// but gathers the brick's D1 voxels into a list and multiplies blocks of 32 of
+// pv_conv_plan_kernel, one workgroup per 8x8x8 brick, makes the bit maps of
+// occupied and D1 voxels (one byte per eight w) and lists each brick's voxels
+// for either convolution; pv_conv3d_rows_kernel multiplies blocks of 32 of
 // them: a fragment read names a voxel per lane, so any 32 voxels of the brick
-// make a block. What bounded the brick with aligned blocks was not the MFMAs
-// but what each wave loads per tap: its weights, 1 KB per 32 channels, whatever
-// the number of its voxels (64 channels a wave: 55 k cycles of the vector
-// cache against 27 k of MFMAs per live brick). Here the waves are WC channel
-// groups x 4/WC voxel groups, each with all its share of the blocks (S at
-// most) and few channels: weights and fragment reads then cost less than the
-// MFMAs.
+// make a block.
 //
 // The halo is compact: 32 bytes a voxel, 336 a row of ten, so that voxel
 // (u, v, w) starts in 16-byte bank 2w + 2u + 5v (mod 16) plus a constant, under
-// every tap. Sixteen lanes are served together: the list deals the voxels so
+// every tap. Sixteen lanes are served together: a list deals the voxels so
 // that position p holds a voxel of bank class p mod 16 as far as the classes
 // reach, and the reads do not conflict.
-//
-// Input modes: occ, a sparse grid (voxels of count 0 read as zero; their rows
-// may be unwritten); with occ_dense, a whole grid of which occ gives only the
-// points' voxels; CB: the output of such a convolution, whose rows exist in D1
-// (bits d1, one byte per eight w) and are elsewhere the constant of its batch
-// norm bn_in, which the halo takes from a table.
-// d1_out: the convolution writes its D1 bits for the next one.
-// Outputs outside D1 are not written.
 // ---------------------------------------------------------------------------
 constexpr int kRowsRow = kHalo * 32 + 16;              // 336
 constexpr int kRowsHalo = kHalo * kHalo * kRowsRow;    // 33600 per buffer
-constexpr int kRowsMaxCin = 256;                       // CB: the constant's table
+constexpr int kRowsMaxCin = 256;                       // the constant's table
+constexpr int kListLen = 512;                          // entries per brick
+constexpr uint16_t kNoVoxel = 0xffff;
 
-template <int NB, int WC, int S, bool VEC, bool CB>
+// The D1 bits of row (ru, rv) of a brick from its halo's occupied bits.
+__device__ __forceinline__ uint32_t d1_row(const uint32_t* s_occ, int ru, int rv) {
+    uint32_t m = 0u;
+#pragma unroll
+    for (int du = 0; du < 3; du++)
+#pragma unroll
+        for (int dv = 0; dv < 3; dv++) m |= s_occ[(ru + du) * kHalo + rv + dv];
+    return m | (m >> 1) | (m >> 2);
+}
+
+// Deals the voxels marked in `need` (row tid / 4 of the brick, of which this
+// thread takes two) into s_row. deal_rank counts the bank classes into s_cls
+// (zero on entry); after a barrier deal_place stores the voxels (s_row all
+// kNoVoxel on entry) and returns the number of blocks of 32. A voxel's order
+// within its class is that of the atomics and does not matter: each output's
+// arithmetic is its own.
+struct DealRank {
+    int rank[2], cls[2];
+};
+__device__ __forceinline__ DealRank deal_rank(uint32_t need, int tid, int* s_cls) {
+    const int ru = tid >> 5, rv = (tid >> 2) & 7, rw = (tid & 3) * 2;
+    DealRank d;
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+        d.cls[i] = (2 * (rw + i) + 2 * ru + 5 * rv) & 15;
+        d.rank[i] = (need >> (rw + i)) & 1u ? atomicAdd(&s_cls[d.cls[i]], 1) : -1;
+    }
+    return d;
+}
+__device__ __forceinline__ int deal_place(const DealRank& d, int tid, const int* s_cls,
+                                          uint16_t* s_row) {
+    int total = 0;
+#pragma unroll
+    for (int c = 0; c < 16; c++) total += s_cls[c];
+    const int P = (total + 15) >> 4;  // groups of sixteen
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+        if (d.rank[i] < 0) continue;
+        int pos = d.rank[i] * 16 + d.cls[i];
+        if (d.rank[i] >= P) {
+            // past the class's share: the places other classes leave
+            int e = d.rank[i] - P;
+            for (int c = 0; c < d.cls[i]; c++) e += max(s_cls[c] - P, 0);
+            int c = 0;
+            while (c < 15 && e >= max(P - s_cls[c], 0)) e -= max(P - s_cls[c++], 0);
+            pos = (s_cls[c] + e) * 16 + c;
+        }
+        s_row[pos] = (uint16_t)((tid >> 2) * 8 + (tid & 3) * 2 + i);
+    }
+    return __builtin_amdgcn_readfirstlane((P + 1) >> 1);
+}
+
+// The occupied bits of a brick's halo rows, from the counts. Ends before the
+// barrier that completes them; s_occ is zeroed here, behind a barrier.
+__device__ __forceinline__ void halo_occupied(const int32_t* __restrict__ counts, size_t cloud,
+                                              int R, int u0, int v0, int w0, int tid,
+                                              uint32_t* s_occ) {
+    int n[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const int h = tid + i * 256;
+        const int gu = u0 + h / (kHalo * kHalo) - 1, gv = v0 + (h / kHalo) % kHalo - 1,
+                  gw = w0 + h % kHalo - 1;
+        n[i] = 0;
+        if (h < kHaloVox && gu >= 0 && gu < R && gv >= 0 && gv < R && gw >= 0 && gw < R)
+            n[i] = counts[cloud + ((size_t)gu * R + gv) * R + gw];
+    }
+    if (tid < kHalo * kHalo) s_occ[tid] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const int h = tid + i * 256;
+        if (n[i] > 0) atomicOr(&s_occ[h / kHalo], 1u << (h % kHalo));
+    }
+}
+
+// list[0], n[0]: D1; list[1], n[1]: the voxels read, which are those holding
+// points (nearest), or the corner cells of the points at pn, or without pn D1
+// (then list[1] is not made).
+__global__ __launch_bounds__(256) void pv_conv_plan_kernel(
+    const int32_t* __restrict__ counts, const float* __restrict__ pn, int N, int nearest, int R,
+    int nbr, PvConvPlan plan) {
+    __shared__ uint32_t s_occ[kHalo * kHalo];  // halo rows
+    __shared__ uint32_t s_read[kBrick * kBrick];
+    constexpr int kPlanNear = 1024;
+    __shared__ float s_near_p[kPlanNear][3];
+    __shared__ int s_near;
+    __shared__ __attribute__((aligned(16))) int s_cls[2][16];
+    __shared__ uint16_t s_row[2][kListLen];
+    const int tid = threadIdx.x;
+    const int brick = blockIdx.x;
+    int r = brick;
+    const int bw = r % nbr;
+    r /= nbr;
+    const int bv = r % nbr;
+    r /= nbr;
+    const int bu = r % nbr;
+    const int b = r / nbr;
+    const int u0 = bu * kBrick, v0 = bv * kBrick, w0 = bw * kBrick;
+    const size_t cloud = (size_t)b * R * R * R;
+    if (tid < kBrick * kBrick) s_read[tid] = 0u;
+    if (tid == 0) s_near = 0;
+    if (tid < 32) s_cls[tid >> 4][tid & 15] = 0;
+    ((uint32_t*)s_row)[tid] = 0xffffffffu;
+    ((uint32_t*)s_row)[tid + 256] = 0xffffffffu;
+    // The few points near the brick (most waves hold one) are gathered first,
+    // so that the fp64 cells are formed once per 64 of them.
+    const float* p = pn + (size_t)b * N * 3;
+    const int lane = tid & 63;
+    auto mark = [&](float x, float y, float z) {
+        const PvAxis ax = pv_trilinear_axis(x, R), ay = pv_trilinear_axis(y, R),
+                     az = pv_trilinear_axis(z, R);
+        const int a0 = az.i0 - w0, a1 = az.i1 - w0;
+        const uint32_t wbits = (a0 >= 0 && a0 < kBrick ? 1u << a0 : 0u) |
+                               (a1 >= 0 && a1 < kBrick ? 1u << a1 : 0u);
+        if (wbits == 0u) return;
+#pragma unroll
+        for (int c = 0; c < 4; c++) {
+            const int u = (c & 2 ? ax.i1 : ax.i0) - u0, v = (c & 1 ? ay.i1 : ay.i0) - v0;
+            if (u >= 0 && u < kBrick && v >= 0 && v < kBrick)
+                atomicOr(&s_read[u * kBrick + v], wbits);
+        }
+    };
+    // A thread has U points in flight: two runs of four (three 16-byte loads
+    // each, where the cloud's rows allow), 1024 points apart.
+    constexpr int U = 8;
+    float q[U][3];
+    const bool whole = ((uintptr_t)p & 15u) == 0 && (N & 3) == 0;
+    auto point = [&](int j0, int i) { return j0 + (i >> 2) * 1024 + tid * 4 + (i & 3); };
+    auto load_points = [&](int j0) {
+#pragma unroll
+        for (int h = 0; h < U / 4; h++) {
+            const int j = point(j0, 4 * h);
+            if (whole) {
+                const float4* s = (const float4*)(p + (size_t)min(j, N - 4) * 3);
+                const float4 a = s[0], c = s[1], e = s[2];
+                const float v[12] = {a.x, a.y, a.z, a.w, c.x, c.y, c.z, c.w, e.x, e.y, e.z, e.w};
+#pragma unroll
+                for (int i = 0; i < 12; i++) q[4 * h + i / 3][i % 3] = v[i];
+            } else {
+#pragma unroll
+                for (int i = 0; i < 12; i++)
+                    q[4 * h + i / 3][i % 3] = p[(size_t)min(j + i / 3, N - 1) * 3 + i % 3];
+            }
+        }
+    };
+    auto gather_near = [&](int j0) {
+        const float fR = (float)R;
+        uint64_t close[U];
+        int n = 0;
+#pragma unroll
+        for (int i = 0; i < U; i++) {
+            // the exact cells lie within 1.5 of R x - 1/2 (NaN passes)
+            const float x = q[i][0] * fR, y = q[i][1] * fR, z = q[i][2] * fR;
+            const bool far = x < u0 - 2 || x > u0 + kBrick + 2 || y < v0 - 2 ||
+                             y > v0 + kBrick + 2 || z < w0 - 2 || z > w0 + kBrick + 2;
+            close[i] = __ballot(!far && point(j0, i) < N);
+            n += __popcll(close[i]);
+        }
+        if (n == 0) return;
+        int at = 0;
+        if (lane == 0) at = atomicAdd(&s_near, n);
+        at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+        for (int i = 0; i < U; i++) {
+            if ((close[i] >> lane) & 1ull) {
+                const int k = at + __popcll(close[i] & ((1ull << lane) - 1ull));
+                if (k < kPlanNear) {
+                    s_near_p[k][0] = q[i][0];
+                    s_near_p[k][1] = q[i][1];
+                    s_near_p[k][2] = q[i][2];
+                } else {
+                    mark(q[i][0], q[i][1], q[i][2]);  // no room
+                }
+            }
+            at += __popcll(close[i]);
+        }
+    };
+    if (pn) load_points(0);  // in flight beside the counts
+    halo_occupied(counts, cloud, R, u0, v0, w0, tid, s_occ);
+    __syncthreads();
+    const int ru = tid >> 5, rv = (tid >> 2) & 7;
+    const bool in_row = u0 + ru < R && v0 + rv < R;
+    const uint32_t in_w = in_row ? (w0 + kBrick <= R ? 0xffu : (1u << (R - w0)) - 1u) : 0u;
+    const uint32_t occ = (s_occ[(ru + 1) * kHalo + rv + 1] >> 1) & in_w;
+    const uint32_t near = d1_row(s_occ, ru, rv) & in_w;
+    if (in_row && (tid & 3) == 0) {
+        const size_t at = (((size_t)b * R + u0 + ru) * R + v0 + rv) * nbr + bw;
+        plan.occ[at] = (uint8_t)occ;
+        plan.d1[at] = (uint8_t)near;
+    }
+    // no occupied voxel in or beside the brick: no point reads it
+    if (!__syncthreads_or((int)near)) return;
+    if (pn)
+        for (int j0 = 0;;) {
+            gather_near(j0);
+            j0 += 256 * U;
+            if (j0 >= N) break;
+            load_points(j0);
+        }
+    if (pn) {
+        __syncthreads();  // s_near's points
+        for (int k = tid; k < min(s_near, kPlanNear); k += 256)
+            mark(s_near_p[k][0], s_near_p[k][1], s_near_p[k][2]);
+        __syncthreads();
+    }
+    const int lists = plan.list[1] ? 2 : 1;
+    const uint32_t need[2] = {near, nearest ? occ : s_read[ru * kBrick + rv] & in_w};
+    DealRank d[2];
+#pragma unroll
+    for (int q = 0; q < 2; q++)
+        if (q < lists) d[q] = deal_rank(need[q], tid, s_cls[q]);
+    __syncthreads();
+    int blocks[2] = {0, 0};
+#pragma unroll
+    for (int q = 0; q < 2; q++)
+        if (q < lists) blocks[q] = deal_place(d[q], tid, s_cls[q], s_row[q]);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+        if (tid < blocks[q] * 16)  // 32 entries a block, two a thread
+            ((uint32_t*)(plan.list[q] + (size_t)brick * kListLen))[tid] = ((uint32_t*)s_row[q])[tid];
+        if (tid == q && blocks[q] > 0) {
+            const int at = blocks[q] * kPvPlanSub + brick % kPvPlanSub;
+            const int k = atomicAdd(&plan.count[q][at], 1);
+            plan.order[q][(size_t)at * ((gridDim.x + kPvPlanSub - 1) / kPvPlanSub) + k] = brick;
+        }
+    }
+}
+
+// One convolution over the listed voxels; rows that are not listed are not
+// written. A workgroup owns a brick and 32*NB channels. What bounded aligned
+// blocks with every wave on all 64 channels was not the MFMAs but what a wave
+// loads per tap: its weights, 1 KB per 32 channels, whatever the number of its
+// voxels (55 k cycles of the vector cache, 64 B a cycle, against 27 k of MFMAs
+// per live brick); and a wave of 32 channels reads a voxel fragment from LDS,
+// 1 KB, for every MFMA, as much as LDS gives at the MFMAs' rate. So the waves
+// are, by what the brick holds:
+//  * NB = 4, four to eight blocks: two by two, 64 channels and half of the
+//    blocks each; more than eight are two items;
+//  * NB = 4, up to kAbreast blocks: four abreast, 32 channels and every block
+//    each: half the weight loads;
+//  * NB = 2: two by two, 32 channels and half of the blocks each;
+//  * NB = 1 (small grids): four voxel groups.
+// Workgroups take the bricks by falling number of blocks, from the plan's
+// buckets: with bricks of 1 to 16 blocks in grid order, a tenth of the work ran
+// on alone for a third of the time.
+// SELF (counts given): the workgroup makes its brick's D1 list itself, and
+// the first tile's stores it and D1's bits in `made` for the next convolution.
+// For grids whose workgroups are all resident at once, where the order is of
+// no use and the plan's launch (5 to 6 us) costs more than it saves.
+// Input modes: bits says which rows exist; the others are zero, or with KONST
+// (the output of such a convolution, bits D1) the constant of its batch norm
+// bn_in, or with dense exist too.
+constexpr int kAbreast = 3;
+// The order in which a NB = 4 convolution takes the bricks: by the blocks of
+// their items. Entry i (4 bits): the brick's blocks - 1.
+constexpr uint64_t kOrderHalved = 0x01234895ab6cd7efull;
+constexpr uint64_t kOrderWhole = 0x0123456789abcdefull;
+
+template <int NB, bool VEC, bool KONST, bool SELF>
 __global__ __launch_bounds__(256, 2) void pv_conv3d_rows_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ wpk, PvBnFold bn,
     PvBnFold bn_in, float neg, uint16_t* __restrict__ y, int R, int Cin, int Cout, int nbr,
-    int nblocks, int B, const int32_t* __restrict__ occ, int occ_dense,
-    const uint8_t* __restrict__ d1, uint8_t* __restrict__ d1_out) {
-    constexpr int NBW = NB / WC, VG = 4 / WC, NT = NB * 32;
-    static_assert(NB % WC == 0 && VG * S >= 16, "the waves hold every block of the brick");
+    int nblocks, int B, const uint8_t* __restrict__ bits, int dense,
+    const uint16_t* __restrict__ list, const uint8_t* __restrict__ nlist,
+    const int32_t* __restrict__ order, const int32_t* __restrict__ bucket,
+    const int32_t* __restrict__ counts, PvConvPlan made) {
+    static_assert(!SELF || (!KONST && NB == 1), "the first convolution of a small grid");
+    constexpr int NT = NB * 32;
     __shared__ __attribute__((aligned(16))) char lds[2 * kRowsHalo];
-    __shared__ __attribute__((aligned(16))) uint16_t s_const[CB ? kRowsMaxCin : 8];
+    __shared__ __attribute__((aligned(16))) uint16_t s_const[KONST ? kRowsMaxCin : 8];
     __shared__ __attribute__((aligned(16))) float bn_tab[2][NT];
-    __shared__ uint32_t s_bits[kHalo * kHalo];  // halo rows: occupied, or (CB) D1
-    __shared__ __attribute__((aligned(16))) int s_cls[16];
-    __shared__ uint16_t s_row[512];
+    __shared__ uint32_t s_bits[kHalo * kHalo];
+    __shared__ __attribute__((aligned(16))) int s_cls[SELF ? 16 : 4];
+    __shared__ uint16_t s_row[SELF ? kListLen : 2];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wg = wave / WC, wc = wave % WC;
-    // every XCD takes one contiguous eighth of every cloud, rotated by the
-    // cloud: a brick's work follows its cloud's occupancy
-    int bid = blockIdx.x;
-    const int per = nblocks / B;
-    if ((per & 7) == 0) {
-        const int xcd = bid & 7, k = bid >> 3, c = k / (per >> 3), j = k % (per >> 3);
-        bid = c * per + ((xcd + c) & 7) * (per >> 3) + j;
-    } else if ((nblocks & 7) == 0) {
-        bid = (bid & 7) * (nblocks >> 3) + (bid >> 3);
-    }
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // --- this workgroup's brick and tile
     const int ntiles = (Cout + NT - 1) / NT;
-    const int nt = bid % ntiles;
-    bid /= ntiles;
-    const int bw = bid % nbr;
-    bid /= nbr;
-    const int bv = bid % nbr;
-    bid /= nbr;
-    const int bu = bid % nbr;
-    const int b = bid / nbr;
+    const int bricks = B * nbr * nbr * nbr;
+    int brick, nt, blocks = 0, first = 0;  // `blocks` of the list from `first`
+    if (SELF || !order) {
+        // each XCD takes one contiguous eighth of every cloud
+        int bid = blockIdx.x;
+        const int per = nblocks / B;
+        if ((per & 7) == 0) {
+            const int xcd = bid & 7, k = bid >> 3, c = k / (per >> 3), j = k % (per >> 3);
+            bid = c * per + ((xcd + c) & 7) * (per >> 3) + j;
+        }
+        nt = bid % ntiles;
+        brick = bid / ntiles;
+        if constexpr (!SELF) blocks = nlist[brick];
+    } else {
+        // lane l holds two buckets of one size: their bricks, items (a brick's
+        // tiles, and its halves past eight blocks) and the items before them
+        static_assert(kPvPlanSub == 8, "two of a size's eight buckets a lane");
+        constexpr uint64_t sizes = NB == 4 ? kOrderHalved : kOrderWhole;
+        const int size = (int)(sizes >> (4 * (lane >> 2)) & 15ull) + 1;
+        const int2 c2 = *(const int2*)(bucket + size * kPvPlanSub + (lane & 3) * 2);
+        const int each = NB == 4 && size > 8 ? 2 * ntiles : ntiles;
+        const int items = (c2.x + c2.y) * each;
+        int before = items;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(before, off, 64);
+            if (lane >= off) before += o;
+        }
+        const uint64_t past = __ballot((int)blockIdx.x < before);
+        if (past == 0ull) return;  // more workgroups than items
+        const int l = __builtin_ctzll(past);
+        const int T = __builtin_amdgcn_readlane(each, l);
+        const int c0 = __builtin_amdgcn_readlane(c2.x, l);
+        const int C = c0 + __builtin_amdgcn_readlane(c2.y, l);
+        const int i = blockIdx.x - __builtin_amdgcn_readlane(before - items, l);
+        // items of a brick 8 apart (on the same XCD) as far as groups of eight
+        // bricks go
+        int k, t;
+        if (i < C / 8 * 8 * T) {
+            k = i / (8 * T) * 8 + (i & 7);
+            t = i % (8 * T) >> 3;
+        } else {
+            const int rest = C & 7, i1 = i - C / 8 * 8 * T;
+            k = C / 8 * 8 + i1 % rest;
+            t = i1 / rest;
+        }
+        blocks = __builtin_amdgcn_readlane(size, l);
+        const int from = blocks * kPvPlanSub + (l & 3) * 2 + (k >= c0 ? 1 : 0);
+        brick = order[(size_t)from * ((bricks + kPvPlanSub - 1) / kPvPlanSub) + k -
+                      (k >= c0 ? c0 : 0)];
+        nt = t % ntiles;
+        if (NB == 4 && blocks > 8) {  // the first or the second half of the list
+            const int half = (blocks + 1) / 2;
+            first = t / ntiles * half;
+            blocks = first ? blocks - half : half;
+        }
+    }
+    int r = brick;
+    const int bw = r % nbr;
+    r /= nbr;
+    const int bv = r % nbr;
+    r /= nbr;
+    const int bu = r % nbr;
+    const int b = r / nbr;
     const int u0 = bu * kBrick, v0 = bv * kBrick, w0 = bw * kBrick, n0 = nt * NT;
     const size_t cloud = (size_t)b * R * R * R;
     const int nch = (Cin + kKC - 1) / kKC;
 
     // --- the halo's bits
-    if (tid < 16) s_cls[tid] = 0;
-    ((uint32_t*)s_row)[tid] = 0xffffffffu;  // no voxel
-    if constexpr (CB) {
-        if (tid < kHalo * kHalo) {
-            const int gu = u0 + tid / kHalo - 1, gv = v0 + tid % kHalo - 1;
-            uint32_t m = 0u;
-            if (gu >= 0 && gu < R && gv >= 0 && gv < R) {
-                const uint8_t* p = d1 + (((size_t)b * R + gu) * R + gv) * nbr + bw;
-                m = (uint32_t)p[0] << 1;
-                if (bw > 0) m |= p[-1] >> 7;
-                if (bw + 1 < nbr) m |= (uint32_t)(p[1] & 1u) << 9;
-            }
-            s_bits[tid] = m;
+    if constexpr (SELF) {
+        if (tid < 16) s_cls[tid] = 0;
+        ((uint32_t*)s_row)[tid] = 0xffffffffu;
+        halo_occupied(counts, cloud, R, u0, v0, w0, tid, s_bits);
+    } else if (tid < kHalo * kHalo) {
+        const int gu = u0 + tid / kHalo - 1, gv = v0 + tid % kHalo - 1;
+        uint32_t m = 0u;
+        if (gu >= 0 && gu < R && gv >= 0 && gv < R) {
+            const uint8_t* p = bits + (((size_t)b * R + gu) * R + gv) * nbr + bw;
+            m = (uint32_t)p[0] << 1;
+            if (bw > 0) m |= p[-1] >> 7;
+            if (bw + 1 < nbr) m |= (uint32_t)(p[1] & 1u) << 9;
         }
+        s_bits[tid] = m;
+    }
+    if constexpr (KONST)
         for (int c = tid; c < Cin; c += 256) {
             float sc, sh;
             pv_bn_coeffs(bn_in, c, sc, sh);
-            const float r = 0.f * sc + sh;
-            s_const[c] = pv_f32_to_bf16(r >= 0.f ? r : r * neg);
+            const float k = 0.f * sc + sh;
+            s_const[c] = pv_f32_to_bf16(k >= 0.f ? k : k * neg);
         }
-    } else {
-        int n[4];
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const int h = tid + i * 256;
-            const int gu = u0 + h / (kHalo * kHalo) - 1, gv = v0 + (h / kHalo) % kHalo - 1,
-                      gw = w0 + h % kHalo - 1;
-            n[i] = 0;
-            if (h < kHaloVox && gu >= 0 && gu < R && gv >= 0 && gv < R && gw >= 0 && gw < R)
-                n[i] = occ[cloud + ((size_t)gu * R + gv) * R + gw];
-        }
-        if (tid < kHalo * kHalo) s_bits[tid] = 0u;
+    if (tid < NT) {  // channels past Cout take the last one's (never stored)
+        float sc, sh;
+        pv_bn_coeffs(bn, min(n0 + tid, Cout - 1), sc, sh);
+        bn_tab[0][tid] = sc;
+        bn_tab[1][tid] = sh;
+    }
+    __syncthreads();
+    if constexpr (SELF) {
+        const int ru = tid >> 5, rv = (tid >> 2) & 7;
+        const bool in_row = u0 + ru < R && v0 + rv < R;
+        const uint32_t in_w = in_row ? (w0 + kBrick <= R ? 0xffu : (1u << (R - w0)) - 1u) : 0u;
+        const uint32_t near = d1_row(s_bits, ru, rv) & in_w;
+        const bool store = made.d1 && nt == 0;
+        if (store && in_row && (tid & 3) == 0)
+            made.d1[(((size_t)b * R + u0 + ru) * R + v0 + rv) * nbr + bw] = (uint8_t)near;
+        const DealRank d = deal_rank(near, tid, s_cls);
         __syncthreads();
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const int h = tid + i * 256;
-            if (n[i] > 0) atomicOr(&s_bits[h / kHalo], 1u << (h % kHalo));
+        blocks = deal_place(d, tid, s_cls, s_row);
+        __syncthreads();
+        if (store) {
+            if (tid == 0) made.n[brick] = (uint8_t)blocks;
+            if (tid < blocks * 16)
+                ((uint32_t*)(made.list[0] + (size_t)brick * kListLen))[tid] =
+                    ((uint32_t*)s_row)[tid];
         }
     }
-    __syncthreads();
-
-    // --- the list of the brick's D1 voxels: thread tid takes two of row
-    // (ru, rv). Their order within a bank class is that of the atomics and
-    // does not matter: each output's arithmetic is its own.
-    const int ru = tid >> 5, rv = (tid >> 2) & 7, rw = (tid & 3) * 2;
-    uint32_t need;
-    if constexpr (CB) {
-        need = s_bits[(ru + 1) * kHalo + rv + 1] >> 1;
-    } else {
-        uint32_t m = 0u;
-#pragma unroll
-        for (int du = 0; du < 3; du++)
-#pragma unroll
-            for (int dv = 0; dv < 3; dv++) m |= s_bits[(ru + du) * kHalo + rv + dv];
-        need = m | (m >> 1) | (m >> 2);
-    }
-    const bool in_row = u0 + ru < R && v0 + rv < R;
-    need &= in_row ? (w0 + kBrick <= R ? 0xffu : (1u << (R - w0)) - 1u) : 0u;
-    if (!CB && d1_out && nt == 0 && in_row && (tid & 3) == 0)
-        d1_out[(((size_t)b * R + u0 + ru) * R + v0 + rv) * nbr + bw] = (uint8_t)need;
-    int rank[2], cls[2];
-#pragma unroll
-    for (int i = 0; i < 2; i++) {
-        cls[i] = (2 * (rw + i) + 2 * ru + 5 * rv) & 15;
-        rank[i] = (need >> (rw + i)) & 1u ? atomicAdd(&s_cls[cls[i]], 1) : -1;
-    }
-    __syncthreads();
-    int total = 0;
-#pragma unroll
-    for (int c = 0; c < 16; c++) total += s_cls[c];
-    total = __builtin_amdgcn_readfirstlane(total);
-    if (total == 0) return;  // uniform: nothing near a point in this brick
-    const int P = (total + 15) >> 4;  // groups of sixteen
-#pragma unroll
-    for (int i = 0; i < 2; i++) {
-        if (rank[i] < 0) continue;
-        int pos = rank[i] * 16 + cls[i];
-        if (rank[i] >= P) {
-            // past the class's share: the places other classes leave, in order
-            int e = rank[i] - P;
-            for (int c = 0; c < cls[i]; c++) e += max(s_cls[c] - P, 0);
-            int c = 0;
-            while (c < 15 && e >= max(P - s_cls[c], 0)) e -= max(P - s_cls[c++], 0);
-            pos = (s_cls[c] + e) * 16 + c;
-        }
-        s_row[pos] = (uint16_t)(ru * 64 + rv * 8 + rw + i);
-    }
+    blocks = __builtin_amdgcn_readfirstlane(blocks);  // uniform over the workgroup
+    if (blocks == 0) return;
 
     // --- halo pieces of this thread: piece p = set*256 + tid is voxel p/2,
     // channels (p%2)*8 .. +7 of the chunk
@@ -669,90 +931,97 @@ __global__ __launch_bounds__(256, 2) void pv_conv3d_rows_kernel(
     const __amdgpu_buffer_rsrc_t xr =
         make_rsrc(x + cloud * Cin + ulo * slab, (uint32_t)((uhi - ulo) * slab * 2));
     const int pq = tid & 1;
+    auto piece_off = [&](int h, bool& konst) -> int {  // halo voxel h
+        const int hr = h / kHalo, hw = h % kHalo;
+        const int gu = u0 + hr / kHalo - 1, gv = v0 + hr % kHalo - 1, gw = w0 + hw - 1;
+        const bool grid = gu >= 0 && gu < R && gv >= 0 && gv < R && gw >= 0 && gw < R;
+        const bool bit = (s_bits[hr] >> hw) & 1u;
+        konst = KONST && grid && !bit;
+        return grid && (bit || (!KONST && dense))
+                   ? ((((gu - ulo) * R + gv) * R + gw) * Cin + pq * 8) * 2 : kOOB;
+    };
     int goff[kSets], loff[kSets];
-    uint32_t konst = 0u;  // CB: the sets that take the constant
+    uint32_t konst = 0u;  // the sets that take the constant
 #pragma unroll
     for (int set = 0; set < kSets; set++) {
         const int h = min(set * 128 + (tid >> 1), kHaloVox - 1);
-        const int hr = h / kHalo, hu = hr / kHalo, hv = hr % kHalo, hw = h % kHalo;
-        const int gu = u0 + hu - 1, gv = v0 + hv - 1, gw = w0 + hw - 1;
-        const bool grid = gu >= 0 && gu < R && gv >= 0 && gv < R && gw >= 0 && gw < R;
-        const bool bit = (s_bits[hr] >> hw) & 1u;
-        const bool in = grid && (bit || (!CB && occ_dense));
-        if (CB && grid && !bit) konst |= 1u << set;
-        goff[set] = in ? ((((gu - ulo) * R + gv) * R + gw) * Cin + pq * 8) * 2 : kOOB;
-        loff[set] = hr * kRowsRow + hw * 32 + pq * 16;
+        bool k;
+        goff[set] = piece_off(h, k);
+        konst |= (k ? 1u : 0u) << set;
+        loff[set] = h / kHalo * kRowsRow + h % kHalo * 32 + pq * 16;
     }
-    auto halo_load = [&](int set, int cc) -> uint4 {
-        if (VEC) return bload16(xr, cc + pq * 8 < Cin ? goff[set] : kOOB, cc * 2);
-        return bload8_elems(xr, goff[set], cc * 2, Cin - cc - pq * 8);
+    auto halo_load = [&](int off, int cc) -> uint4 {
+        if (VEC) return bload16(xr, cc + pq * 8 < Cin ? off : kOOB, cc * 2);
+        return bload8_elems(xr, off, cc * 2, Cin - cc - pq * 8);
     };
-    auto halo_store = [&](int set, int off, uint4 v, uint4 kv) {
-        if constexpr (CB) {
+    auto halo_store = [&](int set, int buf, uint4 v, uint4 kv) {
+        if constexpr (KONST) {
             const bool k = (konst >> set) & 1u;
             v.x = k ? kv.x : v.x;
             v.y = k ? kv.y : v.y;
             v.z = k ? kv.z : v.z;
             v.w = k ? kv.w : v.w;
         }
-        *(uint4*)(lds + off + loff[set]) = v;
+        *(uint4*)(lds + buf + loff[set]) = v;
     };
     auto const_of = [&](int cc) -> uint4 {
-        if constexpr (CB)
+        if constexpr (KONST)
             if (cc + pq * 8 < Cin) return *(const uint4*)&s_const[cc + pq * 8];
         return make_uint4(0u, 0u, 0u, 0u);
     };
-
-    const int G = (Cout + 31) / 32;
-    const __amdgpu_buffer_rsrc_t wr = make_rsrc(wpk, (uint32_t)((size_t)nch * kTaps * G * 1024));
-    const int wlane = lane * 16;
-    auto load_w = [&](int c, int tap, pv_bf16x8 (&wf)[NBW]) {
-        const int cc = c < nch ? c : nch - 1;  // past the end: reload, never used
-#pragma unroll
-        for (int nb = 0; nb < NBW; nb++)
-            wf[nb] = as_frag(bload16(wr, wlane,
-                                     ((cc * kTaps + tap) * G + nt * NB + wc * NBW + nb) * 1024));
-    };
-    if (tid < NT) {  // channels past Cout take the last one's (never stored)
-        float sc, sh;
-        pv_bn_coeffs(bn, min(n0 + tid, Cout - 1), sc, sh);
-        bn_tab[0][tid] = sc;
-        bn_tab[1][tid] = sh;
-    }
     {
         const uint4 kv = const_of(0);
 #pragma unroll
-        for (int set = 0; set < kSets; set++) halo_store(set, 0, halo_load(set, 0), kv);
+        for (int set = 0; set < kSets; set++) halo_store(set, 0, halo_load(goff[set], 0), kv);
     }
-    __syncthreads();
 
-    // --- n blocks of this wave: block k*VG + wg of the list in slot k
+    // --- this wave's channels and its share of the blocks: block k*vg + wg in
+    // slot k
+    const bool abreast = NB == 4 && blocks <= kAbreast;
+    const int wc = abreast ? 4 : (NB > 1 ? 2 : 1);  // waves side by side
+    const int vg = 4 / wc, wg = wave / wc;
+    const int cl = wave % wc * (NT / wc);  // the first channel in the tile
+    const int G = (Cout + 31) / 32;
+    const __amdgpu_buffer_rsrc_t wr = make_rsrc(wpk, (uint32_t)((size_t)nch * kTaps * G * 1024));
+    const int wlane = lane * 16, wgrp = (n0 + cl) / 32;
     const int r32 = lane & 31, khalf = lane >> 5;
-    const int blocks = (P + 1) >> 1;
-    auto run = [&](auto count) {
-        constexpr int n = decltype(count)::value;
-        constexpr int kWD = n > 4 ? 2 : 8, kWR = kWD + 1, kHaloLag = 4;
+    const uint16_t* mylist =
+        (SELF ? s_row : list + (size_t)brick * kListLen) + (first + wg) * 32 + r32;
+    auto run = [&](auto count, auto width) {
+        constexpr int n = decltype(count)::value, W = decltype(width)::value;
+        // Fragments are read two taps ahead where few MFMAs pass in a tap
+        // (an LDS read takes about as long as four of them).
+        constexpr int kWD = n * W > 4 ? 2 : 8, kWR = kWD + 1, kHaloLag = 4,
+                      kBD = n * W > 4 ? 1 : 2, kBR = kBD + 1;
         static_assert(kTaps % kWR == 0, "the weight ring realigns at every chunk");
         constexpr int nr = n > 0 ? n : 1;
-        int base[nr];
+        int vox[nr], base[nr];
 #pragma unroll
-        for (int k = 0; k < n; k++) {
-            const int vox = s_row[(k * VG + wg) * 32 + r32] & 511;  // none: any voxel
-            base[k] = ((vox >> 6) * kHalo + ((vox >> 3) & 7)) * kRowsRow + (vox & 7) * 32 +
-                      khalf * 16;
-        }
-        pv_f32x16 acc[nr][NBW];
+        for (int k = 0; k < n; k++) vox[k] = k * vg + wg < blocks ? mylist[k * vg * 32] : kNoVoxel;
+        pv_bf16x8 wf[kWR][W];
+        auto load_w = [&](int c, int tap, pv_bf16x8 (&f)[W]) {
+            const int cc = c < nch ? c : nch - 1;  // past the end: reload, never used
 #pragma unroll
-        for (int i = 0; i < n; i++)
-#pragma unroll
-            for (int j = 0; j < NBW; j++)
-#pragma unroll
-                for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
-        pv_bf16x8 wf[kWR][NBW];
+            for (int j = 0; j < W; j++)
+                f[j] = as_frag(bload16(wr, wlane, ((cc * kTaps + tap) * G + wgrp + j) * 1024));
+        };
         if (n > 0) {
 #pragma unroll
             for (int k = 0; k < kWD; k++) load_w(0, k, wf[k]);
         }
+#pragma unroll
+        for (int k = 0; k < n; k++) {
+            const int v = vox[k] & 511;  // none: any voxel
+            base[k] = ((v >> 6) * kHalo + ((v >> 3) & 7)) * kRowsRow + (v & 7) * 32 + khalf * 16;
+        }
+        pv_f32x16 acc[nr][W];
+#pragma unroll
+        for (int i = 0; i < n; i++)
+#pragma unroll
+            for (int j = 0; j < W; j++)
+#pragma unroll
+                for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
+        __syncthreads();  // chunk 0's halo is stored
         for (int c = 0; c < nch; c++) {
             const int cur_off = (c & 1) * kRowsHalo, nxt_off = kRowsHalo - cur_off;
             // past the last chunk the next halo loads out of range (zeros):
@@ -761,48 +1030,41 @@ __global__ __launch_bounds__(256, 2) void pv_conv3d_rows_kernel(
             // their registers.
             const int cn = c + 1 < nch ? (c + 1) * kKC : Cin;
             const uint4 kv = const_of(cn);
-            pv_bf16x8 bf[2][nr];
+            pv_bf16x8 bf[kBR][nr];
             uint4 hr[kHaloLag];
+            auto read_b = [&](int tn) {
+                const int off = ((tn / 9) * kHalo + (tn / 3) % 3) * kRowsRow + (tn % 3) * 32;
 #pragma unroll
-            for (int k = 0; k < n; k++)
-                bf[0][k] = *(const pv_bf16x8*)(lds + base[k] + cur_off);
+                for (int k = 0; k < n; k++)
+                    bf[tn % kBR][k] = *(const pv_bf16x8*)(lds + base[k] + off + cur_off);
+            };
+#pragma unroll
+            for (int t = 0; t < kBD; t++) read_b(t);
 #pragma unroll
             for (int t = 0; t < kTaps; t++) {
                 if (n > 0) {
-                    if (t + kWD < kTaps)
-                        load_w(c, t + kWD, wf[(t + kWD) % kWR]);
-                    else
-                        load_w(c + 1, t + kWD - kTaps, wf[(t + kWD) % kWR]);
+                    if (t + kWD < kTaps) load_w(c, t + kWD, wf[(t + kWD) % kWR]);
+                    else load_w(c + 1, t + kWD - kTaps, wf[(t + kWD) % kWR]);
                 }
                 if (VEC && t >= kHaloLag && t < kSets + kHaloLag)
                     halo_store(t - kHaloLag, nxt_off, hr[(t - kHaloLag) % kHaloLag], kv);
-                if (VEC && t < kSets) hr[t % kHaloLag] = halo_load(t, cn);
-                if (t + 1 < kTaps) {
-                    const int tn = t + 1;
-                    const int off = ((tn / 9) * kHalo + (tn / 3) % 3) * kRowsRow + (tn % 3) * 32;
-#pragma unroll
-                    for (int k = 0; k < n; k++)
-                        bf[tn & 1][k] = *(const pv_bf16x8*)(lds + base[k] + off + cur_off);
-                }
+                if (VEC && t < kSets) hr[t % kHaloLag] = halo_load(goff[t], cn);
+                if (t + kBD < kTaps) read_b(t + kBD);
 #pragma unroll
                 for (int k = 0; k < n; k++)
 #pragma unroll
-                    for (int nb = 0; nb < NBW; nb++)
-                        acc[k][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                            wf[t % kWR][nb], bf[t & 1][k], acc[k][nb], 0, 0, 0);
+                    for (int j = 0; j < W; j++)
+                        acc[k][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            wf[t % kWR][j], bf[t % kBR][k], acc[k][j], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (!VEC && c + 1 < nch) {
 #pragma unroll 1
                 for (int p = tid; p < kPieces; p += 256) {
-                    const int h = p >> 1, h_r = h / kHalo, hw = h % kHalo;
-                    const int gu = u0 + h_r / kHalo - 1, gv = v0 + h_r % kHalo - 1,
-                              gw = w0 + hw - 1;
-                    const bool in = gu >= 0 && gu < R && gv >= 0 && gv < R && gw >= 0 && gw < R &&
-                                    (occ_dense || ((s_bits[h_r] >> hw) & 1u));
-                    *(uint4*)(lds + nxt_off + h_r * kRowsRow + hw * 32 + pq * 16) = bload8_elems(
-                        xr, in ? ((((gu - ulo) * R + gv) * R + gw) * Cin + pq * 8) * 2 : kOOB,
-                        cn * 2, Cin - cn - pq * 8);
+                    bool k;
+                    const int h = p >> 1, off = piece_off(h, k);
+                    *(uint4*)(lds + nxt_off + h / kHalo * kRowsRow + h % kHalo * 32 + pq * 16) =
+                        halo_load(off, cn);
                 }
             }
             pv_lds_barrier();  // LDS only: the weight prefetch stays in flight
@@ -810,42 +1072,55 @@ __global__ __launch_bounds__(256, 2) void pv_conv3d_rows_kernel(
         // lane l holds voxel l % 32 of a block and channels 8j + 4 (l / 32) + i
 #pragma unroll
         for (int k = 0; k < n; k++) {
-            const int vox = s_row[(k * VG + wg) * 32 + r32];
-            if (vox >= 512) continue;
-            uint16_t* row = y + (cloud + ((size_t)(u0 + (vox >> 6)) * R + v0 + ((vox >> 3) & 7)) * R +
-                                 w0 + (vox & 7)) * Cout;
+            const int v = vox[k];
+            if (v >= kListLen) continue;
+            uint16_t* row = y + (cloud + ((size_t)(u0 + (v >> 6)) * R + v0 + ((v >> 3) & 7)) * R +
+                                 w0 + (v & 7)) * Cout;
 #pragma unroll
-            for (int nb = 0; nb < NBW; nb++)
+            for (int w = 0; w < W; w++)
 #pragma unroll
                 for (int j = 0; j < 4; j++) {
-                    const int nl = (wc * NBW + nb) * 32 + 8 * j + 4 * khalf;
+                    const int nl = cl + 32 * w + 8 * j + 4 * khalf;
                     if (n0 + nl >= Cout) continue;
                     const float4 sc = *(const float4*)&bn_tab[0][nl];
                     const float4 sh = *(const float4*)&bn_tab[1][nl];
-                    float r[4] = {acc[k][nb][4 * j + 0] * sc.x + sh.x,
-                                  acc[k][nb][4 * j + 1] * sc.y + sh.y,
-                                  acc[k][nb][4 * j + 2] * sc.z + sh.z,
-                                  acc[k][nb][4 * j + 3] * sc.w + sh.w};
+                    float q[4] = {acc[k][w][4 * j + 0] * sc.x + sh.x,
+                                  acc[k][w][4 * j + 1] * sc.y + sh.y,
+                                  acc[k][w][4 * j + 2] * sc.z + sh.z,
+                                  acc[k][w][4 * j + 3] * sc.w + sh.w};
 #pragma unroll
-                    for (int e = 0; e < 4; e++) r[e] = r[e] >= 0.f ? r[e] : r[e] * neg;
+                    for (int e = 0; e < 4; e++) q[e] = q[e] >= 0.f ? q[e] : q[e] * neg;
                     *(uint2*)(row + n0 + nl) =
-                        make_uint2(pv_pack_bf16x2(r[0], r[1]), pv_pack_bf16x2(r[2], r[3]));
+                        make_uint2(pv_pack_bf16x2(q[0], q[1]), pv_pack_bf16x2(q[2], q[3]));
                 }
         }
     };
-    const int mine = __builtin_amdgcn_readfirstlane((blocks - wg + VG - 1) / VG);
-    switch (mine) {  // one straight loop for each number of blocks
-        case 0: run(std::integral_constant<int, 0>{}); break;
-        case 1: run(std::integral_constant<int, 1>{}); break;
-        case 2: run(std::integral_constant<int, 2>{}); break;
-        case 3: run(std::integral_constant<int, 3>{}); break;
-        case 4: run(std::integral_constant<int, 4>{}); break;
-        default:
-            if constexpr (S > 4) {
-                if (mine <= 6) run(std::integral_constant<int, 6>{});
-                else run(std::integral_constant<int, 8>{});
-            }
+    // one straight loop for each number of blocks
+#define PV_RUN(N_, W_) run(std::integral_constant<int, N_>{}, std::integral_constant<int, W_>{})
+    const int mine = (blocks - wg + vg - 1) / vg;
+    if constexpr (NB == 4) {
+        if (abreast) {
+            if (mine == 1) PV_RUN(1, 1);
+            else if (mine == 2) PV_RUN(2, 1);
+            else PV_RUN(3, 1);
+        } else {
+            if (mine <= 2) PV_RUN(2, 2);
+            else if (mine == 3) PV_RUN(3, 2);
+            else PV_RUN(4, 2);
+        }
+    } else {
+        switch (mine) {
+            case 0: PV_RUN(0, 1); break;
+            case 1: PV_RUN(1, 1); break;
+            case 2: PV_RUN(2, 1); break;
+            case 3: PV_RUN(3, 1); break;
+            case 4: PV_RUN(4, 1); break;
+            case 5:
+            case 6: if constexpr (NB == 2) PV_RUN(6, 1); break;
+            default: if constexpr (NB == 2) PV_RUN(8, 1);
+        }
     }
+#undef PV_RUN
 }
 
 // Repack bf16 weights [Cout][27][Cin] into the fragment order the MFMA conv
@@ -987,22 +1262,42 @@ void launch_bf16(const void* x, int B, int R, int Cin, int Cout, const void* w,
 #undef PV_CONV
 }
 
-template <int NB, int WC, int S>
+template <int NB>
 void launch_rows(const PvConvRows& c, const PvBnFold& bn, float neg, bool vec, hipStream_t s) {
+    constexpr bool SMALL = NB == 1;
     const int nbr = (c.R + kBrick - 1) / kBrick;
-    const int blocks = c.B * nbr * nbr * nbr * ((c.Cout + NB * 32 - 1) / (NB * 32));
-#define PV_ROWS_CONV(V, CBX)                                                                  \
-    hipLaunchKernelGGL((pv_conv3d_rows_kernel<NB, WC, S, V, CBX>), dim3(blocks), dim3(256), 0, s, \
-                       (const uint16_t*)c.x, (const uint16_t*)c.packed, bn, c.bn_in, neg,       \
-                       (uint16_t*)c.y, c.R, c.Cin, c.Cout, nbr, blocks, c.B, c.occ,             \
-                       (int)c.occ_dense, c.d1, c.d1_out)
-    if (c.d1)
-        PV_ROWS_CONV(true, true);
-    else if (vec)
-        PV_ROWS_CONV(true, false);
-    else
-        PV_ROWS_CONV(false, false);
+    int blocks = c.B * nbr * nbr * nbr * ((c.Cout + NB * 32 - 1) / (NB * 32));
+    if (NB == 4) blocks *= 2;  // halves of bricks with more than eight blocks
+#define PV_ROWS_CONV(V, K, SELFX)                                                             \
+    hipLaunchKernelGGL((pv_conv3d_rows_kernel<NB, V, K, SELFX>), dim3(blocks), dim3(256), 0, s,  \
+                       (const uint16_t*)c.x, (const uint16_t*)c.packed, bn, c.bn_in, neg,        \
+                       (uint16_t*)c.y, c.R, c.Cin, c.Cout, nbr, blocks, c.B,                     \
+                       c.input == PvConvRows::kRowsOfFirst ? c.plan.d1 : c.plan.occ,             \
+                       (int)(c.input == PvConvRows::kWhole), c.plan.list[c.which],               \
+                       c.plan.n, SMALL ? nullptr : c.plan.order[c.which],                        \
+                       c.plan.count[c.which], c.counts, made)
+    PvConvPlan made{};
+    if (c.input == PvConvRows::kRowsOfFirst) {
+        PV_ROWS_CONV(true, true, false);
+    } else if constexpr (SMALL) {
+        if (c.which == 0) made = c.plan;
+        if (vec)
+            PV_ROWS_CONV(true, false, true);
+        else
+            PV_ROWS_CONV(false, false, true);
+    } else if (vec) {
+        PV_ROWS_CONV(true, false, false);
+    } else {
+        PV_ROWS_CONV(false, false, false);
+    }
 #undef PV_ROWS_CONV
+}
+
+// Grids of fewer than 512 tiles of 64 channels (two a CU) take 32-channel
+// tiles and no plan: their workgroups are resident at once.
+bool rows_small(int B, int R, int Cout) {
+    const int nbr = (R + kBrick - 1) / kBrick;
+    return Cout % 64 != 0 || (long)B * nbr * nbr * nbr * (Cout / 64) < 512;
 }
 
 }  // namespace
@@ -1130,8 +1425,50 @@ bool pv_conv3d_rows_ok(int B, int R, int Cin, int Cout, int n_convs) {
            (n_convs < 2 || pv_conv3d_splits(B, R, Cout, Cout) == 1);
 }
 
-size_t pv_conv3d_rows_d1_bytes(int B, int R) {
-    return (size_t)B * R * R * ((R + kBrick - 1) / kBrick);
+PvConvPlan pv_conv_plan_carve(void* base, int B, int R, size_t* bytes) {
+    const int nbr = (R + kBrick - 1) / kBrick;
+    const size_t bricks = (size_t)B * nbr * nbr * nbr;
+    size_t off = 0;
+    auto take = [&](size_t n) {
+        char* q = (char*)base + off;
+        off += pv_align256(n);
+        return q;
+    };
+    PvConvPlan plan{};
+    plan.count[0] = (int32_t*)take(kPvPlanCounts * sizeof(int32_t));
+    plan.count[1] = plan.count[0] + kPvPlanCounts / 2;
+    plan.occ = (uint8_t*)take((size_t)B * R * R * nbr);
+    plan.d1 = (uint8_t*)take((size_t)B * R * R * nbr);
+    plan.n = (uint8_t*)take(bricks);
+    for (int q = 0; q < 2; q++) {
+        plan.list[q] = (uint16_t*)take(bricks * kListLen * sizeof(uint16_t));
+        plan.order[q] = (int32_t*)take(17 * kPvPlanSub *
+                                       ((bricks + kPvPlanSub - 1) / kPvPlanSub) * sizeof(int32_t));
+    }
+    *bytes = off;
+    return plan;
+}
+
+pvconv_status pv_launch_conv_plan(PvConvPlan& plan, const int32_t* counts, const float* pn,
+                                  bool nearest, int B, int N, int R, int Cout, hipStream_t s) {
+    const int nbr = (R + kBrick - 1) / kBrick;
+    const int nb3 = nbr * nbr * nbr;
+    // Every brick's workgroup reads its cloud's points: 2.1 M of them (16
+    // clouds of 2048 points, 64 bricks each) cost ~2 us and save a third of
+    // the last convolution's MFMAs. Past four times that, and on small grids,
+    // the last convolution computes D1.
+    const bool small = rows_small(B, R, Cout);
+    if (nearest || (long long)B * nb3 * N > (8ll << 20)) pn = nullptr;
+    if (small || (!nearest && !pn)) plan.list[1] = nullptr;
+    if (!small)
+        hipLaunchKernelGGL(pv_conv_plan_kernel, dim3(B * nb3), dim3(256), 0, s, counts, pn, N,
+                           (int)nearest, R, nbr, plan);
+    if (!plan.list[1]) {
+        plan.list[1] = plan.list[0];
+        plan.order[1] = plan.order[0];
+        plan.count[1] = plan.count[0];
+    }
+    return pv_launch_status();
 }
 
 pvconv_status pv_launch_conv3d_rows(const PvConvRows& c, const PvBnFold& bn, int act, float slope,
@@ -1140,9 +1477,13 @@ pvconv_status pv_launch_conv3d_rows(const PvConvRows& c, const PvBnFold& bn, int
     const bool vec = c.Cin % 8 == 0 && pv_aligned16(c.x);
     const int nbr = (c.R + kBrick - 1) / kBrick;
     const long bricks = (long)c.B * nbr * nbr * nbr;
-    if (c.Cout % 64 == 0 && bricks * (c.Cout / 64) >= 512)
-        launch_rows<2, 2, 8>(c, bn, neg, vec, s);
+    if (rows_small(c.B, c.R, c.Cout))
+        launch_rows<1>(c, bn, neg, vec, s);
+    else if (c.Cout % 128 == 0 && bricks >= 512)
+        // about half of the bricks are live: 128 channels an item need twice
+        // the CUs in bricks
+        launch_rows<4>(c, bn, neg, vec, s);
     else
-        launch_rows<1, 1, 4>(c, bn, neg, vec, s);
+        launch_rows<2>(c, bn, neg, vec, s);
     return pv_launch_status();
 }

@@ -98,6 +98,8 @@ struct PvPackJob {
 struct PvPackJobs {
     PvPackJob job[PVCONV_MAX_CONVS];
     int n;
+    int32_t* zero;  // or NULL: nzero words cleared by the first workgroup
+    int nzero;
 };
 
 // ---- internal launchers (arguments already validated) ---------------------
@@ -136,6 +138,8 @@ constexpr int kPvPackTaps = 27;
 // tid: the thread's index within its 256-thread share of the workgroup.
 __device__ __forceinline__ void pv_pack_role(const PvPackJobs& jobs, int blk,
                                              int tid = threadIdx.x) {
+    if (blk == 0 && jobs.zero)
+        for (int i = tid; i < jobs.nzero; i += 256) jobs.zero[i] = 0;
     int q = 0;
     while (q + 1 < jobs.n && blk >= jobs.job[q].blocks) blk -= jobs.job[q++].blocks;
     const PvPackJob& J = jobs.job[q];
@@ -177,21 +181,50 @@ pvconv_status pv_launch_conv3d(const void* x, int B, int R, int Cin, int Cout, c
                                const PvBnFold& bn, int act, float slope, bool bf16, void* y,
                                bool out_bf16, void* ws, hipStream_t s, bool packed = false,
                                float* split_ws = nullptr, const int32_t* occ = nullptr);
-// A convolution inside a layer's forward that computes only D1, the voxels
-// within one voxel of an occupied one (bf16 grids, packed weights).
+// The voxels that the convolutions inside a layer's forward compute: bit maps
+// (one byte per eight w) of the occupied voxels and of D1, the voxels within
+// one voxel of an occupied one, and per 8x8x8 brick the voxels a first (0:
+// D1) and a last (1: those the devoxelisation reads) convolution computes, in
+// blocks of 32. The bricks with n blocks lie in kPvPlanSub buckets (brick mod
+// kPvPlanSub: one counter for all took 5 us of the plan's atomics), bucket
+// n * kPvPlanSub + s of order[q] holding count[q][..] of them; the
+// kPvPlanCounts words from count[0] have to be zero (PvPackJobs::zero) before
+// the plan is made. Without a plan launch (small grids) the first convolution
+// fills d1, list[0] and n (the blocks of each brick) instead.
+constexpr int kPvPlanSub = 8;
+constexpr int kPvPlanCounts = 2 * 17 * kPvPlanSub;
+struct PvConvPlan {
+    uint8_t* occ;
+    uint8_t* d1;
+    uint8_t* n;
+    uint16_t* list[2];
+    int32_t* order[2];
+    int32_t* count[2];
+};
+// The plan's arrays in a workspace (256-byte aligned) of *bytes.
+PvConvPlan pv_conv_plan_carve(void* base, int B, int R, size_t* bytes);
+// counts [B][R^3]: the points per voxel; pn [B][N][3]: their normalised
+// coordinates, at whose corner cells (nearest: voxels) the grid is read.
+pvconv_status pv_launch_conv_plan(PvConvPlan& plan, const int32_t* counts, const float* pn,
+                                  bool nearest, int B, int N, int R, int Cout, hipStream_t s);
+// A convolution inside a layer's forward that computes the voxels of one of
+// the plan's lists (bf16 grids, packed weights).
 struct PvConvRows {
     const void* x;       // [B][R^3][Cin] bf16
     const void* packed;  // pv_pack_job's weights
-    void* y;             // [B][R^3][Cout] bf16, written in D1 only
+    void* y;             // [B][R^3][Cout] bf16, written at the listed voxels only
     int B, R, Cin, Cout;
-    const int32_t* occ;  // the points' counts [B][R^3]; unless occ_dense, x is
-    bool occ_dense;      // zero (its rows unread) where they are 0
-    uint8_t* d1_out;     // or NULL: D1's bits, one byte per eight w
-    const uint8_t* d1;   // or NULL: x is the output of such a convolution with
-    PvBnFold bn_in;      // these bits, this batch norm and the same activation
+    PvConvPlan plan;     // made by pv_launch_conv_plan, for these B, R and Cout
+    int which;           // the list
+    const int32_t* counts;  // the points per voxel
+    enum Input {
+        kOccupied,       // x is zero (its rows unread) outside the occupied voxels
+        kWhole,          // every row of x exists
+        kRowsOfFirst,    // x is the output of such a convolution with list 0,
+    } input;             // batch norm bn_in and the same activation
+    PvBnFold bn_in;
 };
 bool pv_conv3d_rows_ok(int B, int R, int Cin, int Cout, int n_convs);
-size_t pv_conv3d_rows_d1_bytes(int B, int R);
 pvconv_status pv_launch_conv3d_rows(const PvConvRows& c, const PvBnFold& bn, int act, float slope,
                                     hipStream_t s);
 int pv_conv3d_splits(int B, int R, int Cin, int Cout);

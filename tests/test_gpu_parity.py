@@ -894,6 +894,67 @@ def test_forward_computes_every_voxel_the_devoxelisation_reads(n_convs, devox, R
     assert torch.equal(got, want)
 
 
+def _list_cloud(kind, B, N):
+    rng = np.random.default_rng(N)
+    if kind == "cube":
+        return synth.uniform_cube(rng, B, N)
+    if kind == "clustered":
+        return synth.clustered(rng, B, N)
+    if kind == "knot":  # nearly all points in one brick, two far apart set the scale
+        xyz = rng.normal(scale=0.02, size=(B, N, 3)).astype(np.float32)
+        xyz[:, 0], xyz[:, 1] = -1.0, 1.0
+        return xyz
+    return synth.part_shapes(rng, B, N)
+
+
+@pytest.mark.parametrize("B,N,cin,cout,R,n_convs,devox,cloud", [
+    # 64-channel tiles; element-wise input rows; three convolutions (the last
+    # one's input is whole)
+    (16, 2048, 64, 64, 32, 2, "trilinear", "shapes"),
+    (8, 2048, 3, 64, 32, 2, "trilinear", "shapes"),
+    (8, 2048, 16, 64, 32, 3, "trilinear", "shapes"),
+    # 128-channel items: points in odd numbers (unaligned clouds), bricks of up
+    # to sixteen blocks in two halves, more points near one brick than the
+    # plan gathers, nearest neighbour
+    (8, 1023, 64, 128, 32, 2, "trilinear", "shapes"),
+    (8, 4096, 32, 128, 32, 2, "trilinear", "cube"),
+    (8, 3000, 32, 128, 32, 2, "trilinear", "knot"),
+    (8, 1500, 32, 256, 31, 1, "nearest", "shapes"),
+    # small grids: ragged grids and channels, element-wise rows, one voxel
+    (2, 1000, 24, 40, 20, 2, "trilinear", "shapes"),
+    (5, 777, 9, 64, 16, 2, "trilinear", "cube"),
+    (5, 600, 64, 128, 17, 3, "nearest", "shapes"),
+    (64, 3, 8, 8, 1, 2, "trilinear", "cube"),
+    # large clouds: dense grids; more than 512 bricks a cloud
+    (1, 65536, 64, 64, 64, 2, "trilinear", "clustered"),
+    (1, 5001, 16, 64, 72, 2, "trilinear", "cube"),
+])
+def test_forward_convolves_the_listed_voxels_alone(B, N, cin, cout, R, n_convs, devox, cloud):
+    # as above (a workspace of NaN bytes, the bits of the separate calls), over
+    # the forms of the listed convolutions
+    rng = np.random.default_rng(R * 3 + cin)
+    L = synth.draw_pvconv(rng, cin, cout, R, n_convs, bf16=True)
+    L.devox = devox
+    layer = pv.DeviceLayer(L, "cuda", torch.bfloat16)
+    coords = dev(_list_cloud(cloud, B, N))
+    feats = dev(rng.normal(size=(B, N, cin)).astype(np.float32))
+    size = pv.pvconv_forward_workspace_size(B, N, layer)
+    ws = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda")
+    want = pv.pvconv_forward(coords, feats, layer, workspace=ws)
+    h, _, ids, pn = pv.pvconv_voxelize(coords, feats, R, grid_dtype=torch.bfloat16)
+    for i in range(n_convs):
+        h = pv.pvconv_conv3d(h, layer.conv_w[i], R, bn=layer.conv_bn[i], act="leaky",
+                             slope=L.slope, out_dtype=torch.bfloat16)
+    dv = (pv.pvconv_devoxelize_nearest(h, R, ids) if devox == "nearest"
+          else pv.pvconv_devoxelize(h, R, pn))
+    got = pv.pvconv_point_mlp(feats, layer.mlp_w, bias=layer.mlp_b, bn=layer.mlp_bn,
+                              act="relu", residual=dv)
+    assert torch.isfinite(want).all()
+    assert torch.equal(got, want)
+    # and again in a workspace that holds another call's plan
+    assert torch.equal(pv.pvconv_forward(coords, feats, layer, workspace=ws), want)
+
+
 def test_forward_on_a_side_stream_and_repeatable():
     wl = synth.make_workload(2, B=2)
     layer = pv.DeviceLayer(wl.layers[0], "cuda", torch.bfloat16)
