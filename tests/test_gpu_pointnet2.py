@@ -242,3 +242,52 @@ def test_three_interpolate_into_a_column_slice():
     pv.pvconv_three_interpolate(feats, gi, gw, out=wide[:, :, 10:26])
     assert torch.equal(wide[:, :, 10:26], pv.pvconv_three_interpolate(feats, gi, gw))
     assert torch.all(wide[:, :, :10] == 0) and torch.all(wide[:, :, 26:] == 0)
+
+
+@pytest.mark.parametrize("fdt", ["f32", "bf16"])
+@pytest.mark.parametrize("odt", ["f32", "bf16"])
+@pytest.mark.parametrize("C,nsample", [(8, 1), (64, 32), (40, 5), (13, 7), (5, 3)])
+def test_rows_in_pieces_of_eight_are_the_rows_one_by_one(C, nsample, fdt, odt):
+    # grouping, interpolation and the neighbour maximum take eight channels at
+    # once where the rows are aligned; rows shifted off 16 bytes take the
+    # element-wise forms, and the bits are the same. Nothing is written beside
+    # the rows.
+    tdt = {"f32": torch.float32, "bf16": torch.bfloat16}
+    B, N, M = 3, 150, 33
+    xyz = dev(_rooms(B, N, C)[0])
+    rng = np.random.default_rng(C)
+    centers = xyz[:, :M].contiguous()
+    idx = torch.as_tensor(rng.integers(0, N, size=(B, M, nsample)), dtype=torch.int32).cuda()
+    wide = torch.zeros((B, N, C + 16), dtype=tdt[fdt], device="cuda")
+    src = dev(rng.normal(size=(B, N, C)).astype(np.float32)).to(tdt[fdt])
+
+    def rows(off):
+        wide[:, :, off:off + C] = src
+        return wide[:, :, off:off + C]
+
+    def outs(shape, off, width):
+        buf = torch.full(shape + (width + 32,), 7.0, dtype=tdt[odt], device="cuda")
+        return buf, buf[..., off:off + width]
+
+    def beside(buf, off, width):
+        return bool((buf[..., :off] == 7).all()) and bool((buf[..., off + width:] == 7).all())
+
+    nn_idx, nn_w = pv.pvconv_three_nn(xyz, centers)
+    deep = src[:, :M]
+    got = []
+    for off in (8, 1):
+        buf, o = outs((B, M, nsample), off, 3 + C)
+        pv.pvconv_group_points(xyz, rows(off), centers, idx, out=o)
+        assert beside(buf, off, 3 + C)
+        buf2, o2 = outs((B, N), off, C)
+        wide[:, :M, off:off + C] = deep
+        pv.pvconv_three_interpolate(wide[:, :M, off:off + C].contiguous() if off == 8 else
+                                    deep.contiguous(), nn_idx, nn_w, out=o2)
+        assert beside(buf2, off, C)
+        r = rows(off).reshape(B * N, C) if off == 8 else src.reshape(B * N, C).contiguous()
+        buf3, o3 = outs((B * 50,), off, C)
+        pv.pvconv_group_max(r, 3, out=o3)
+        assert beside(buf3, off, C)
+        got.append((o.clone(), o2.clone(), o3.clone()))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
