@@ -128,12 +128,13 @@ __device__ __forceinline__ Axis trilinear_axis(float x, int R) {
 // every axis, its base cell i0 and i1 = min(i0 + 1, R - 1), so the points
 // that reach cell (u, v, w) have base cells in {u-1, u} x {v-1, v} x
 // {w-1, w}. The points are sorted stably by (cloud, base cell) with an LSD
-// radix sort on 8-bit digits (one pass per digit of the cell index; the
-// clouds' entries stay in their own ranges); each cell's range in the
+// radix sort on 8-bit digits (one pass per digit of the cell index, in one
+// launch for clouds of up to kSortSmall points; the clouds' entries stay in
+// their own ranges); each cell's range in the
 // sorted list is recorded with, per sorted point, its eight corner weights
 // (as pv_devoxelize forms them: fp64 products rounded once) and its
 // gradient row (copied into sorted order), and the cells that some point
-// reaches are marked (a byte per cell). One workgroup per 64 consecutive
+// reaches are marked (a byte per cell). One workgroup per few consecutive
 // cells then writes their rows: zeros for unmarked cells, and for marked
 // ones the sum, over the cell's eight candidate base cells in a fixed order
 // and their points in index order, of the point's weight at this cell times
@@ -250,26 +251,158 @@ __global__ __launch_bounds__(64) void pv_radix_scatter_kernel(
     }
 }
 
-// Each cell's range [first, last + 1) in the sorted list (cells without
-// points keep the cleared [0, 0)), the cells the points reach, marked, and
-// (trilinear) per sorted entry its eight corner weights as pv_devoxelize
-// forms them, corner (a, b, c) = offsets (0/1) from the base cell at
-// 4a + 2b + c: fp64 products, rounded once. Where both corners of an axis are the grid's last
-// cell, the upper one's weight is 0.
-__global__ __launch_bounds__(256) void pv_devox_bwd_bounds_kernel(
-    const uint32_t* __restrict__ key, const int32_t* __restrict__ val,
-    const float* __restrict__ pn, int N, size_t E, int R, int2* __restrict__ bounds,
-    float4* __restrict__ rec_w, uint8_t* __restrict__ act) {
+// Clouds of up to kSortSmall points: one workgroup per cloud forms the keys
+// and runs the stable radix passes in LDS. Thread t of wave w holds entries
+// (w*e + c)*64 + lane, c < e; per pass each wave ranks its 64 entries by their
+// 8-bit digit with one ballot per bit and keeps the running counts of its own
+// histogram, the histograms are scanned in (digit, wave) order, and the
+// entries move. The launch's other workgroups clear the ranges and marks. It
+// takes the place of the keys and the passes' launches, whose 4 to 5 us each
+// set the time (2048 points, R = 32: 34 us, 8.7 us so; a bitonic network,
+// 66 dependent LDS steps, took 20.7).
+constexpr int kSortSmall = 4096;
+
+__global__ __launch_bounds__(1024) void pv_devox_bwd_sort_kernel(
+    const float* __restrict__ pn, const int32_t* __restrict__ ids, int R, int B, int N,
+    size_t ncells, uint32_t* __restrict__ key, int32_t* __restrict__ val,
+    int2* __restrict__ bounds, uint32_t* __restrict__ act) {
+    constexpr int NW = 16, E = kSortSmall / 1024;
+    __shared__ uint32_t s_hist[NW][256];
+    __shared__ uint32_t s_key[kSortSmall];
+    __shared__ uint16_t s_val[kSortSmall];
+    __shared__ uint32_t s_sum[4];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if ((int)blockIdx.x >= B) {
+        const size_t stride = (size_t)(gridDim.x - B) * 1024;
+        const size_t t0 = (size_t)(blockIdx.x - B) * 1024 + tid;
+        for (size_t k = t0; k < ncells; k += stride) bounds[k] = make_int2(0, 0);
+        for (size_t k = t0; k < (ncells + 3) / 4; k += stride) act[k] = 0u;
+        return;
+    }
+    const size_t e0 = (size_t)blockIdx.x * N;
+    const int e = (N + 1023) / 1024;
+    uint32_t k[E];
+    int v[E];
+#pragma unroll
+    for (int c = 0; c < E; c++) {
+        const int i = (w * e + c) * 64 + lane;
+        k[c] = 0u;
+        v[c] = -1;
+        if (c < e && i < N) {
+            if (ids) {
+                k[c] = (uint32_t)min(max(ids[e0 + i], 0), R * R * R - 1);
+            } else {
+                const float* p = pn + (e0 + i) * 3;
+                k[c] = (uint32_t)((trilinear_axis(p[0], R).i0 * R + trilinear_axis(p[1], R).i0) * R +
+                                  trilinear_axis(p[2], R).i0);
+            }
+            v[c] = i;
+        }
+    }
+    const uint64_t below = (1ull << lane) - 1ull;
+    for (int shift = 0; shift == 0 || ((R * R * R - 1) >> shift) != 0; shift += 8) {
+        for (int i = tid; i < NW * 256; i += 1024) ((uint32_t*)s_hist)[i] = 0u;
+        __syncthreads();
+        uint32_t rank[E];
+#pragma unroll
+        for (int c = 0; c < E; c++) {
+            if (c >= e) break;
+            const uint32_t d = (k[c] >> shift) & 255u;
+            uint64_t same = __ballot(v[c] >= 0);
+#pragma unroll
+            for (int bit = 0; bit < 8; bit++) {
+                const uint64_t m = __ballot((d >> bit) & 1u);
+                same &= (d >> bit) & 1u ? m : ~m;
+            }
+            // the count so far, then this chunk's, by the first holder; the
+            // wave's LDS accesses are in order
+            const uint32_t before = s_hist[w][d];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (v[c] >= 0 && (same & below) == 0ull) s_hist[w][d] = before + __popcll(same);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            rank[c] = before + __popcll(same & below);
+        }
+        __syncthreads();
+        uint32_t total = 0u;
+        if (tid < 256) {
+            for (int i = 0; i < NW; i++) {
+                const uint32_t n = s_hist[i][tid];
+                s_hist[i][tid] = total;
+                total += n;
+            }
+        }
+        uint32_t incl = total;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t o = (uint32_t)__shfl_up((int)incl, off, 64);
+            if (lane >= off) incl += o;
+        }
+        if (tid < 256 && lane == 63) s_sum[w] = incl;
+        __syncthreads();
+        if (tid < 256) {
+            uint32_t base = incl - total;
+            for (int i = 0; i < w; i++) base += s_sum[i];
+            for (int i = 0; i < NW; i++) s_hist[i][tid] += base;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < E; c++)
+            if (v[c] >= 0) {
+                const uint32_t at = s_hist[w][(k[c] >> shift) & 255u] + rank[c];
+                s_key[at] = k[c];
+                s_val[at] = (uint16_t)v[c];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < E; c++)
+            if (v[c] >= 0) {
+                const int i = (w * e + c) * 64 + lane;  // the places are the same ones
+                k[c] = s_key[i];
+                v[c] = s_val[i];
+            }
+    }
+#pragma unroll
+    for (int c = 0; c < E; c++)
+        if (v[c] >= 0) {
+            const int i = (w * e + c) * 64 + lane;
+            key[e0 + i] = k[c];
+            val[e0 + i] = (int32_t)(e0 + v[c]);
+        }
+}
+
+// Per sorted entry, items of VW channels: the gradient row in sorted order,
+// srow[i] = dout[val[i]]; and with the entry's first item each cell's range
+// [first, last + 1) in the sorted list (cells without points keep the cleared
+// [0, 0)), the cells the points reach, marked, and (trilinear) its eight
+// corner weights as pv_devoxelize forms them, corner (a, b, c) = offsets (0/1)
+// from the base cell at 4a + 2b + c: fp64 products, rounded once. Where both
+// corners of an axis are the grid's last cell, the upper one's weight is 0.
+template <int VW>
+__global__ __launch_bounds__(256) void pv_devox_bwd_rows_kernel(
+    const float* __restrict__ dout, const uint32_t* __restrict__ key,
+    const int32_t* __restrict__ val, const float* __restrict__ pn, int N, int C, size_t items,
+    int R, int2* __restrict__ bounds, float4* __restrict__ rec_w, uint8_t* __restrict__ act,
+    float* __restrict__ srow) {
+    const int per = C / VW;
     const size_t stride = (size_t)gridDim.x * 256;
     const int V = R * R * R;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < E; i += stride) {
+    for (size_t it = (size_t)blockIdx.x * 256 + threadIdx.x; it < items; it += stride) {
+        const size_t i = it / per;
+        const int q = (int)(it - i * per);
+        const int e = val[i];
+        const float* src = dout + (size_t)e * C + q * VW;
+        float* dst = srow + i * C + q * VW;
+        if constexpr (VW == 4)
+            *(float4*)dst = *(const float4*)src;
+        else
+            *dst = *src;
+        if (q != 0) continue;
         const size_t b = i / N;
         const int in = (int)(i - b * N);
         const uint32_t k = key[i];
         int2* bd = bounds + b * V + k;
         if (in == 0 || key[i - 1] != k) bd->x = (int)i;
         if (in == N - 1 || key[i + 1] != k) bd->y = (int)(i + 1);
-        const int e = val[i];
         // the cells this point reaches, marked (every writer stores 1)
         const int ku = (int)(k / (uint32_t)(R * R)), kv = (int)(k / (uint32_t)R) % R,
                   kw = (int)(k % (uint32_t)R);
@@ -293,27 +426,6 @@ __global__ __launch_bounds__(256) void pv_devox_bwd_bounds_kernel(
     }
 }
 
-// The gradient rows in sorted order: srow[i] = dout[val[i]], VW floats per
-// item.
-template <int VW>
-__global__ __launch_bounds__(256) void pv_devox_bwd_rows_kernel(const float* __restrict__ dout,
-                                                                const int32_t* __restrict__ val,
-                                                                int C, size_t items,
-                                                                float* __restrict__ srow) {
-    const int per = C / VW;
-    const size_t stride = (size_t)gridDim.x * 256;
-    for (size_t it = (size_t)blockIdx.x * 256 + threadIdx.x; it < items; it += stride) {
-        const size_t i = it / per;
-        const int q = (int)(it - i * per);
-        const float* src = dout + (size_t)val[i] * C + q * VW;
-        float* dst = srow + i * C + q * VW;
-        if constexpr (VW == 4)
-            *(float4*)dst = *(const float4*)src;
-        else
-            *dst = *src;
-    }
-}
-
 // x / d for 0 <= x < 2^24 and d >= 1, with inv = 1/d in fp32: the product's
 // floor is the quotient or one off it, corrected with the remainder.
 __device__ __forceinline__ int pv_div_small(int x, int d, float inv, int* rem) {
@@ -330,96 +442,105 @@ __device__ __forceinline__ int pv_div_small(int x, int d, float inv, int* rem) {
     return q;
 }
 
-// dG rows: workgroup x takes cells x*64 .. x*64 + 63 (of all clouds' cells
-// in order); every wave reads their marks, so all know which are reached.
-// Items (cell j, channel group q) = threadIdx.x, + 256, ... (walked by
-// constant steps, no divisions): unmarked cells' rows are written as
-// zeros, marked ones as their sums.
+// dG rows, one item (cell, VW channels) per thread and turn: a workgroup takes
+// `cells` consecutive cells a turn (of all clouds' cells in order), as many as
+// its 256 threads have items for. Unmarked cells' rows are written as zeros,
+// marked ones as their sums. A marked item is a chain of three load latencies
+// (mark, ranges, points), so kAhead points are in flight and grids of up to
+// 4096 such workgroups take one turn; larger ones, mostly zeros, take up to
+// four. Whole calls, us, before and now: 3 clouds of 1500 points at R = 16, 64
+// channels 68 and 27; 8 of 2048 at R = 32, 128 channels (134 MB written) 79
+// and 59 (66 with one turn); 65536 clustered points at R = 64 899 and 873.
 template <int VW, bool NEAREST>
 __global__ __launch_bounds__(256) void pv_devox_bwd_gather_kernel(
     const float* __restrict__ srow, const float* __restrict__ rec_w,
-    const int2* __restrict__ bounds, const uint8_t* __restrict__ act, size_t ncells, int R,
-    int C, float* __restrict__ dgrid) {
+    const int2* __restrict__ bounds, const uint8_t* __restrict__ act, size_t ncells, int cells,
+    int turns, int R, int C, float* __restrict__ dgrid) {
     const int per = C / VW;
     const int V = R * R * R, RR = R * R;
     const float invR = 1.f / (float)R, invRR = 1.f / (float)RR;
-    const int lane = threadIdx.x & 63;
-    const int j0 = (int)threadIdx.x / per, q0 = (int)threadIdx.x - j0 * per;
-    const int dj = 256 / per, dq = 256 - dj * per;
-    for (size_t c0 = (size_t)blockIdx.x * 64; c0 < ncells; c0 += (size_t)gridDim.x * 64) {
-        const uint64_t marked = __ballot(c0 + lane < ncells && act[c0 + lane] != 0);
-        const int nc = (int)std::min<size_t>(64, ncells - c0);
-        const size_t b0 = c0 / (size_t)V;  // the chunk's first cell: cloud and index
-        const int cell0 = (int)(c0 - b0 * V);
-        int j = j0, q = q0;
-        while (j < nc) {
-            const size_t cg = c0 + j;
+    const int j = (int)(threadIdx.x / (unsigned)per);
+    if (j >= cells) return;
+    for (int turn = 0; turn < turns; turn++) {
+        const size_t c0 = ((size_t)blockIdx.x * turns + turn) * cells, cg = c0 + j;
+        if (cg >= ncells) return;
+        const bool marked = act[cg] != 0;
+        constexpr int T = NEAREST ? 1 : 8;
+        int from[T], total = 0;   // range t: list entries from[t] + p for p < upto[t]
+        int upto[T];
+        if (marked) {
+            const size_t b = c0 / (size_t)V;  // uniform: the chunk's first cell
+            size_t cell_b = b;
+            int cell = (int)(c0 - b * V) + j;
+            while (cell >= V) {  // the chunk runs into the next cloud
+                cell -= V;
+                cell_b++;
+            }
+            int2 rg[T];
+            if constexpr (NEAREST) {
+                rg[0] = bounds[cg];
+            } else {
+                int rr, w;
+                const int u = pv_div_small(cell, RR, invRR, &rr);
+                const int v = pv_div_small(rr, R, invR, &w);
+                // the base cells (u - 1 .. u, v - 1 .. v, w - 1 .. w) in index
+                // order, whose points reach this cell through their corner 7 - t;
+                // their ranges loaded together
+                const int2* bc = bounds + cell_b * V + ((u - 1) * R + (v - 1)) * R + (w - 1);
+#pragma unroll
+                for (int t = 0; t < T; t++) {
+                    const bool in = ((t & 4) || u > 0) && ((t & 2) || v > 0) && ((t & 1) || w > 0);
+                    rg[t] = in ? bc[(t >> 2) * RR + ((t >> 1) & 1) * R + (t & 1)] : make_int2(0, 0);
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < T; t++) {
+                from[t] = rg[t].x - total;
+                total += rg[t].y - rg[t].x;
+                upto[t] = total;
+            }
+        }
+        for (int q = (int)threadIdx.x - j * per; q < per; q += 256) {
             float acc[VW];
 #pragma unroll
             for (int k = 0; k < VW; k++) acc[k] = 0.f;
-            if ((marked >> j) & 1ull) {
-                int cell = cell0 + j;
-                size_t b = b0;
-                while (cell >= V) {  // the chunk runs into the next cloud
-                    cell -= V;
-                    b++;
+            constexpr int kAhead = 4;
+            for (int p0 = 0; p0 < total; p0 += kAhead) {
+                float r[kAhead][VW], wt[kAhead];
+#pragma unroll
+                for (int i = 0; i < kAhead; i++) {
+                    const int p = min(p0 + i, total - 1);
+                    int off = from[T - 1], corner = 8 - T;
+#pragma unroll
+                    for (int t = T - 2; t >= 0; t--) {
+                        off = p < upto[t] ? from[t] : off;
+                        corner = p < upto[t] ? 7 - t : corner;
+                    }
+                    const size_t si = (size_t)(off + p);
+                    const float* src = srow + si * C + q * VW;
+                    if constexpr (VW == 4) {
+                        const float4 x = *(const float4*)src;
+                        r[i][0] = x.x; r[i][1] = x.y; r[i][2] = x.z; r[i][3] = x.w;
+                    } else {
+                        r[i][0] = *src;
+                    }
+                    if constexpr (!NEAREST) wt[i] = rec_w[si * 8 + corner];
                 }
-                if (NEAREST) {
-                    const int2 rg = bounds[cg];
-#pragma unroll 2
-                    for (int sidx = rg.x; sidx < rg.y; sidx++) {
-                        const float* src = srow + (size_t)sidx * C + q * VW;
-                        if constexpr (VW == 4) {
-                            const float4 x = *(const float4*)src;
-                            acc[0] += x.x; acc[1] += x.y; acc[2] += x.z; acc[3] += x.w;
-                        } else {
-                            acc[0] += *src;
+#pragma unroll
+                for (int i = 0; i < kAhead; i++)
+                    if (p0 + i < total) {
+#pragma unroll
+                        for (int k = 0; k < VW; k++) {
+                            if constexpr (NEAREST) acc[k] += r[i][k];
+                            else acc[k] += wt[i] * r[i][k];
                         }
                     }
-                } else {
-                    int rr, w;
-                    const int u = pv_div_small(cell, RR, invRR, &rr);
-                    const int v = pv_div_small(rr, R, invR, &w);
-                    // the base cells (u - 1 .. u, v - 1 .. v, w - 1 .. w) in
-                    // index order, whose points reach this cell through their
-                    // corner 7 - t; their ranges loaded together
-                    const int2* bc = bounds + b * V + ((u - 1) * R + (v - 1)) * R + (w - 1);
-                    int2 rgs[8];
-#pragma unroll
-                    for (int t = 0; t < 8; t++) {
-                        const bool in =
-                            ((t & 4) || u > 0) && ((t & 2) || v > 0) && ((t & 1) || w > 0);
-                        rgs[t] = in ? bc[(t >> 2) * RR + ((t >> 1) & 1) * R + (t & 1)]
-                                    : make_int2(0, 0);
-                    }
-#pragma unroll
-                    for (int t = 0; t < 8; t++) {
-#pragma unroll 2
-                        for (int sidx = rgs[t].x; sidx < rgs[t].y; sidx++) {
-                            const float wt = rec_w[(size_t)sidx * 8 + (7 - t)];
-                            const float* src = srow + (size_t)sidx * C + q * VW;
-                            if constexpr (VW == 4) {
-                                const float4 x = *(const float4*)src;
-                                acc[0] += wt * x.x; acc[1] += wt * x.y;
-                                acc[2] += wt * x.z; acc[3] += wt * x.w;
-                            } else {
-                                acc[0] += wt * *src;
-                            }
-                        }
-                    }
-                }
             }
             float* dst = dgrid + cg * C + q * VW;
             if constexpr (VW == 4)
                 *(float4*)dst = make_float4(acc[0], acc[1], acc[2], acc[3]);
             else
                 dst[0] = acc[0];
-            j += dj;
-            q += dq;
-            if (q >= per) {
-                q -= per;
-                j++;
-            }
         }
     }
 }
@@ -848,37 +969,44 @@ pvconv_status pv_launch_devoxelize_backward(const float* dout, int B, int N, int
     DevoxBwdWs ws;
     devox_bwd_layout(B, N, C, R, (char*)workspace, &ws);
     const size_t E = (size_t)B * N;
-    const int nch = (N + kSortChunk - 1) / kSortChunk;
     const size_t ncells = (size_t)B * V;
-    const unsigned kb = (unsigned)std::min<size_t>((std::max(E, ncells) + 255) / 256, 4096);
-    hipLaunchKernelGGL(pv_devox_bwd_keys_kernel, dim3(kb), dim3(256), 0, s, pn, ids, R, E, ncells,
-                       ws.key[0], ws.val[0], ws.bounds, (uint32_t*)ws.act);
-    // one pass per 8-bit digit of the largest cell index
     int cur = 0;
-    for (int shift = 0; shift == 0 || ((V - 1) >> shift) != 0; shift += 8) {
-        hipLaunchKernelGGL(pv_radix_hist_kernel, dim3(B * nch), dim3(64), 0, s, ws.key[cur], N, nch,
-                           shift, ws.hist);
-        hipLaunchKernelGGL(pv_radix_scan_kernel, dim3(B), dim3(256), 0, s, ws.hist, N, nch);
-        hipLaunchKernelGGL(pv_radix_scatter_kernel, dim3(B * nch), dim3(64), 0, s, ws.key[cur],
-                           ws.val[cur], ws.key[cur ^ 1], ws.val[cur ^ 1], ws.hist, N, nch, shift);
-        cur ^= 1;
+    if (N <= kSortSmall) {
+        const unsigned zb = (unsigned)std::min<size_t>((ncells + 1023) / 1024, 256);
+        hipLaunchKernelGGL(pv_devox_bwd_sort_kernel, dim3(B + zb), dim3(1024), 0, s, pn, ids, R, B,
+                           N, ncells, ws.key[0], ws.val[0], ws.bounds, (uint32_t*)ws.act);
+    } else {
+        const int nch = (N + kSortChunk - 1) / kSortChunk;
+        const unsigned kb = (unsigned)std::min<size_t>((std::max(E, ncells) + 255) / 256, 4096);
+        hipLaunchKernelGGL(pv_devox_bwd_keys_kernel, dim3(kb), dim3(256), 0, s, pn, ids, R, E,
+                           ncells, ws.key[0], ws.val[0], ws.bounds, (uint32_t*)ws.act);
+        // one pass per 8-bit digit of the largest cell index
+        for (int shift = 0; shift == 0 || ((V - 1) >> shift) != 0; shift += 8) {
+            hipLaunchKernelGGL(pv_radix_hist_kernel, dim3(B * nch), dim3(64), 0, s, ws.key[cur], N,
+                               nch, shift, ws.hist);
+            hipLaunchKernelGGL(pv_radix_scan_kernel, dim3(B), dim3(256), 0, s, ws.hist, N, nch);
+            hipLaunchKernelGGL(pv_radix_scatter_kernel, dim3(B * nch), dim3(64), 0, s, ws.key[cur],
+                               ws.val[cur], ws.key[cur ^ 1], ws.val[cur ^ 1], ws.hist, N, nch,
+                               shift);
+            cur ^= 1;
+        }
     }
-    hipLaunchKernelGGL(pv_devox_bwd_bounds_kernel, dim3(std::min<size_t>(blocks_for(E), 4096)),
-                       dim3(256), 0, s, ws.key[cur], ws.val[cur], ids ? nullptr : pn, N, E, R,
-                       ws.bounds, ws.rec_w, ws.act);
     const bool vec = C % 4 == 0 && ((uintptr_t)dout & 15) == 0 && ((uintptr_t)dgrid & 15) == 0;
     const size_t rows = E * (size_t)(vec ? C / 4 : C);
     const unsigned rb = (unsigned)std::min<size_t>((rows + 255) / 256, 8192);
-    if (vec)
-        hipLaunchKernelGGL(pv_devox_bwd_rows_kernel<4>, dim3(rb), dim3(256), 0, s, dout,
-                           ws.val[cur], C, rows, ws.srow);
-    else
-        hipLaunchKernelGGL(pv_devox_bwd_rows_kernel<1>, dim3(rb), dim3(256), 0, s, dout,
-                           ws.val[cur], C, rows, ws.srow);
-    const unsigned gb = (unsigned)std::min<size_t>((ncells + 63) / 64, (size_t)1 << 20);
+#define PV_DEVOX_ROWS(VW)                                                                        \
+    hipLaunchKernelGGL(pv_devox_bwd_rows_kernel<VW>, dim3(rb), dim3(256), 0, s, dout, ws.key[cur], \
+                       ws.val[cur], ids ? nullptr : pn, N, C, rows, R, ws.bounds, ws.rec_w, ws.act, \
+                       ws.srow)
+    if (vec) PV_DEVOX_ROWS(4); else PV_DEVOX_ROWS(1);
+#undef PV_DEVOX_ROWS
+    const int per = vec ? C / 4 : C, cells = std::max(1, 256 / per);
+    const size_t groups = (ncells + cells - 1) / cells;
+    const int turns = (int)std::min<size_t>(std::max<size_t>(groups / 4096, 1), 4);
+    const unsigned gb = (unsigned)((groups + turns - 1) / turns);
 #define PV_DEVOX_BWD(VW, NEAR)                                                                   \
     hipLaunchKernelGGL((pv_devox_bwd_gather_kernel<VW, NEAR>), dim3(gb), dim3(256), 0, s, ws.srow, \
-                       (const float*)ws.rec_w, ws.bounds, ws.act, ncells, R, C, dgrid)
+                       (const float*)ws.rec_w, ws.bounds, ws.act, ncells, cells, turns, R, C, dgrid)
     if (vec) {
         if (ids) PV_DEVOX_BWD(4, true);
         else PV_DEVOX_BWD(4, false);

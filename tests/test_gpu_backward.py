@@ -85,6 +85,11 @@ DEVOX_BWD_EDGES = [
     (2, 2500, 16, 8, "uniform"),
     (1, 3000, 64, 1, "faces"),
     (4, 1025, 7, 12, "uniform"),
+    # the edges of the LDS sort (one point, a second chunk a wave, its largest
+    # size, three passes) and of the launches that take over past it
+    (3, 1, 4, 4, "uniform"), (2, 129, 3, 4, "faces"), (2, 4096, 20, 4, "uniform"),
+    (2, 4097, 20, 4, "faces"), (1, 2000, 128, 1, "uniform"),
+    (1, 1500, 2, 64, "uniform"),   # crowded cells
 ]
 
 
