@@ -577,9 +577,12 @@ pvconv_status pvconv_forward_ex(const float* coords, const void* feats, pvconv_d
     // of the normalisation launch (or in a launch of their own when the
     // normalisation is skipped)
     PvPackJobs jobs{};
-    if (bf) {
+    const bool rows = bf && pv_conv3d_rows_ok(B, R, L->cin, L->cout, L->n_convs);
+    if (rows) {
         jobs.zero = w.plan.count[0];
         jobs.nzero = kPvPlanCounts;
+    }
+    if (bf) {
         for (int i = 0; i < L->n_convs; i++)
             pv_pack_job(jobs, L->conv_w[i], i ? L->cout : L->cin, L->cout, w.conv_ws[i]);
     }
@@ -605,7 +608,6 @@ pvconv_status pvconv_forward_ex(const float* coords, const void* feats, pvconv_d
     // (nearest), all within one voxel of an occupied voxel, so only those
     // outputs are computed. With one or two convolutions the first one's
     // output is also computed only there, and constant elsewhere.
-    const bool rows = bf && pv_conv3d_rows_ok(B, R, cin, L->cout, L->n_convs);
     if (rows) {
         st = pv_launch_conv_plan(w.plan, w.counts, pnorm, L->devox == PVCONV_DEVOX_NEAREST, B, N,
                                  R, L->cout, s);

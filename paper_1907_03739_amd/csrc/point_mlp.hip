@@ -649,6 +649,32 @@ __global__ __launch_bounds__(256) void pv_point_mlp_f32_kernel(
     }
 }
 
+// fp32 weights and few input channels: one thread per output element.
+template <typename XT>
+__global__ __launch_bounds__(256) void pv_point_mlp_f32_elem_kernel(
+    const XT* __restrict__ x, int x_ld, int M, int Cin, int Cout, const float* __restrict__ w,
+    PvBnFold bn, int act, float slope, const float* __restrict__ cloud_bias, int ppc,
+    const float* __restrict__ residual, int res_ld, void* __restrict__ out, int out_bf16,
+    int out_ld) {
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= (size_t)M * Cout) return;
+    const int n = (int)(i % Cout);
+    const size_t m = i / Cout;
+    const XT* xr = x + m * x_ld;
+    const float* wr = w + (size_t)n * Cin;
+    float s = 0.f;
+    for (int k = 0; k < Cin; k++) s += wr[k] * ld1<XT>(xr + k);
+    if (cloud_bias) s += cloud_bias[(m / ppc) * Cout + n];
+    float scale, shift;
+    pv_bn_coeffs(bn, n, scale, shift);
+    float v = pv_activate(s * scale + shift, act, slope);
+    if (residual) v += residual[m * res_ld + n];
+    if (out_bf16)
+        ((uint16_t*)out)[m * out_ld + n] = pv_f32_to_bf16(v);
+    else
+        ((float*)out)[m * out_ld + n] = v;
+}
+
 template <int NB, typename XT>
 void launch_mfma(const void* x, int x_ld, int M, int Cin, int Cout, const void* w, bool vec,
                  bool c4, const PvBnFold& bn, int act, float slope, const float* cb, int ppc,
@@ -926,6 +952,22 @@ pvconv_status pv_launch_point_mlp(const void* x, bool x_bf16, int x_ld, int M, i
                                       ppc, res, res_ld, out, out_bf16, out_ld, s);
         }
     } else {
+        // Few input channels: the tiles' fixed cost (operands, LDS, barrier:
+        // 3.5 us a call) against a thread per output (us: 2000 x 9 -> 32 3.2,
+        // 8192 x 9 -> 32 4.6, 8192 x 3 -> 32 3.0, 8192 x 16 -> 32 9.7)
+        const size_t total = (size_t)M * Cout;
+        if (Cin <= 8 || (Cin < 16 && total <= 131072)) {
+            const unsigned blocks = (unsigned)((total + 255) / 256);
+            if (x_bf16)
+                hipLaunchKernelGGL(pv_point_mlp_f32_elem_kernel<uint16_t>, dim3(blocks), dim3(256),
+                                   0, s, (const uint16_t*)x, x_ld, M, Cin, Cout, (const float*)w,
+                                   bn, act, slope, cb, ppc, res, res_ld, out, (int)out_bf16, out_ld);
+            else
+                hipLaunchKernelGGL(pv_point_mlp_f32_elem_kernel<float>, dim3(blocks), dim3(256), 0,
+                                   s, (const float*)x, x_ld, M, Cin, Cout, (const float*)w, bn, act,
+                                   slope, cb, ppc, res, res_ld, out, (int)out_bf16, out_ld);
+            return pv_launch_status();
+        }
         // four consecutive values of K are one aligned vector of either row
         const bool vec = Cin % 4 == 0 && pv_aligned16(x) && pv_aligned16(w) &&
                          x_ld % 4 == 0;

@@ -572,8 +572,11 @@ def test_point_mlp_f32_matches_oracle(M, Cin, Cout):
 @pytest.mark.parametrize("M,Cin,Cout,xdt,odt,ppc,off", [
     # tiles of 32 points x 32 channels, K in pieces of 8 over four waves: one
     # point, one value of K, ragged ends of each, K past one turn of the waves
-    (1, 1, 1, "f32", "f32", 0, 0), (31, 4, 33, "f32", "f32", 0, 0),
-    (33, 12, 31, "f32", "bf16", 0, 0), (64, 36, 64, "bf16", "f32", 32, 0),
+    (1, 1, 1, "f32", "f32", 0, 0), (1, 16, 1, "f32", "f32", 0, 0),
+    (31, 20, 33, "f32", "f32", 0, 0), (33, 18, 31, "f32", "bf16", 0, 0),
+    # a thread per output: few input channels, and its last size
+    (31, 4, 33, "f32", "f32", 0, 0), (4096, 12, 32, "bf16", "f32", 0, 0),
+    (4097, 12, 32, "f32", "f32", 0, 0), (64, 36, 64, "bf16", "f32", 32, 0),
     (500, 130, 70, "f32", "f32", 250, 0), (257, 1000, 40, "f32", "f32", 0, 0),
     (100, 64, 32, "f32", "f32", 0, 1),     # rows off 16-byte boundaries
     (100, 64, 32, "bf16", "f32", 0, 1), (96, 20, 8, "bf16", "bf16", 0, 4),
