@@ -827,6 +827,10 @@ def bench_layer(args, wl, dev, cold=True, peaks=True, cpu_seconds=None):
             k["forward_form"] = ("the forward runs the same kernel without the empty voxels' "
                                  "zero rows (its first convolution reads them as zero through "
                                  "the counts) and with the weight packing in extra workgroups")
+        if bf16 and n.startswith("conv") and L.n_convs <= 2:
+            k["forward_form"] = ("the forward lists the voxels that are read and multiplies "
+                                 "those alone (pv_conv_plan_kernel, pv_conv3d_rows_kernel); "
+                                 "timed here is the complete grid")
         if cold_ms:
             ms_cold = statistics.median(cold_ms[n])
             rate_cold = amount / (ms_cold * 1e-3) / (1e9 if unit == "GB/s" else 1e12)
