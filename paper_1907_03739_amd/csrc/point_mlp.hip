@@ -26,6 +26,22 @@ namespace {
 
 constexpr int kWaves = 4;
 
+// out_bf16 where rows of eight channels are whole 16-byte pieces of the output.
+// Lanes l and l + 32 hold channels 8g .. 8g+3 and 8g+4 .. 8g+7 of one point;
+// the halves swapped, lane l has all of group g (a) and lane l + 32 all of the
+// next (b), and a store writes 32 bytes of a row rather than 16: the stores of
+// all workgroups go out at once and the number of row pieces they touch is what
+// they wait for (16384 x 512 -> 2048: 58 us with 8-byte stores, 49 with 16;
+// 131072 x 35 -> 32 -> 32 -> 64: 29.2, 26.0).
+constexpr int kBf16Rows8 = 2;
+__device__ __forceinline__ uint4 swap_rows8(const float4& a, const float4& b) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(pv_pack_bf16x2(a.x, a.y),
+                                                     pv_pack_bf16x2(b.x, b.y), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(pv_pack_bf16x2(a.z, a.w),
+                                                     pv_pack_bf16x2(b.z, b.w), false, false);
+    return uint4{lo[0], hi[0], lo[1], hi[1]};
+}
+
 template <typename XT>
 __device__ __forceinline__ pv_bf16x8 load_a8(const XT* p, bool full, int valid);
 
@@ -313,8 +329,21 @@ __global__ __launch_bounds__(kWaves * 64) void pv_point_mlp_tile_kernel(
             res[nb][g].z += v[2];
             res[nb][g].w += v[3];
         }
-    if (!mrow) return;
     const size_t orow = (size_t)(m0 + r32) * out_ld;
+    if constexpr (C4) {
+        if (out_bf16 == kBf16Rows8) {
+#pragma unroll
+            for (int nb = 0; nb < NB; nb++)
+#pragma unroll
+                for (int g = 0; g < 4; g += 2) {
+                    const uint4 o = swap_rows8(res[nb][g], res[nb][g + 1]);
+                    const int c = nb * 32 + (g + h) * 8;
+                    if (mrow && c < ncols) *(uint4*)((uint16_t*)out + orow + n0 + c) = o;
+                }
+            return;
+        }
+    }
+    if (!mrow) return;
 #pragma unroll
     for (int nb = 0; nb < NB; nb++)
 #pragma unroll
@@ -533,6 +562,15 @@ __global__ __launch_bounds__(64 * WN * WM, 1) void pv_point_mlp_lds_kernel(
                 val[g] = float4{v[0] + rs.x, v[1] + rs.y, v[2] + rs.z, v[3] + rs.w};
             }
             if (blk + 1 < MB * NB) load_ext((blk + 1) / NB, (blk + 1) % NB);
+            if (out_bf16 == kBf16Rows8) {
+#pragma unroll
+                for (int g = 0; g < 4; g += 2) {
+                    const uint4 o = swap_rows8(val[g], val[g + 1]);
+                    const int nl = wn * NB * 32 + nb * 32 + (g + khalf) * 8;
+                    if (m < M && n0 + nl < Cout) *(uint4*)((uint16_t*)out + orow + n0 + nl) = o;
+                }
+                continue;
+            }
 #pragma unroll
             for (int g = 0; g < 4; g++) {
                 const int nl = wn * NB * 32 + nb * 32 + g * 8 + 4 * khalf;
@@ -675,6 +713,11 @@ __global__ __launch_bounds__(256) void pv_point_mlp_f32_elem_kernel(
         ((float*)out)[m * out_ld + n] = v;
 }
 
+int out_kind(const void* out, bool out_bf16, int out_ld, int Cout) {
+    if (!out_bf16) return 0;
+    return Cout % 8 == 0 && out_ld % 8 == 0 && pv_aligned16(out) ? kBf16Rows8 : 1;
+}
+
 template <int NB, typename XT>
 void launch_mfma(const void* x, int x_ld, int M, int Cin, int Cout, const void* w, bool vec,
                  bool c4, const PvBnFold& bn, int act, float slope, const float* cb, int ppc,
@@ -684,7 +727,8 @@ void launch_mfma(const void* x, int x_ld, int M, int Cin, int Cout, const void* 
 #define PV_TILE(V, C)                                                                         \
     hipLaunchKernelGGL((pv_point_mlp_tile_kernel<NB, XT, V, C>), g, dim3(kWaves * 64), 0, s, \
                        (const XT*)x, x_ld, M, Cin, Cout, (const uint16_t*)w, bn, act, slope,   \
-                       cb, ppc, res, res_ld, out, (int)out_bf16, out_ld, PvDevoxIn{})
+                       cb, ppc, res, res_ld, out, out_kind(out, out_bf16, out_ld, Cout),       \
+                       out_ld, PvDevoxIn{})
     if (vec) {
         if (c4) PV_TILE(true, true); else PV_TILE(true, false);
     } else {
@@ -704,13 +748,13 @@ void launch_lds(const void* x, int x_ld, int M, int Cin, int Cout, const void* w
     if (cb || res)
         hipLaunchKernelGGL((pv_point_mlp_lds_kernel<NB, MB, WN, WM, XT, true>), dim3(nblocks),
                            dim3(S::NTHR), 0, s, (const XT*)x, x_ld, M, Cin, Cout, (const uint16_t*)w,
-                           bn, act, slope, cb, ppc, res, res_ld, out, (int)out_bf16, out_ld, ntn,
-                           nblocks);
+                           bn, act, slope, cb, ppc, res, res_ld, out,
+                           out_kind(out, out_bf16, out_ld, Cout), out_ld, ntn, nblocks);
     else
         hipLaunchKernelGGL((pv_point_mlp_lds_kernel<NB, MB, WN, WM, XT, false>), dim3(nblocks),
                            dim3(S::NTHR), 0, s, (const XT*)x, x_ld, M, Cin, Cout, (const uint16_t*)w,
-                           bn, act, slope, cb, ppc, res, res_ld, out, (int)out_bf16, out_ld, ntn,
-                           nblocks);
+                           bn, act, slope, cb, ppc, res, res_ld, out,
+                           out_kind(out, out_bf16, out_ld, Cout), out_ld, ntn, nblocks);
 }
 
 // ---- small-M path --------------------------------------------------------
@@ -1005,7 +1049,7 @@ pvconv_status pv_launch_devox_point_mlp(const PvDevoxIn& dv, const void* x, bool
                        dim3((M + kWaves * 32 - 1) / (kWaves * 32), (Cout + NB * 32 - 1) / (NB * 32)), \
                        dim3(kWaves * 64), 0, s, (const XT*)x, x_ld, M, Cin, Cout,              \
                        (const uint16_t*)w, bn, act, slope, nullptr, 1, nullptr, 0, out,         \
-                       (int)out_bf16, out_ld, dv)
+                       out_kind(out, out_bf16, out_ld, Cout), out_ld, dv)
     if (x_bf16) PV_DV(2, uint16_t); else PV_DV(2, float);
 #undef PV_DV
     return pv_launch_status();

@@ -608,6 +608,31 @@ def test_point_mlp_f32_edges_of_its_tiles(M, Cin, Cout, xdt, odt, ppc, off):
         assert_dot_f32(host(out), ref, mag, "mlp fp32")
 
 
+@pytest.mark.parametrize("M,Cin,Cout", [
+    (128, 16, 8), (129, 35, 24), (160, 64, 40), (300, 64, 136), (257, 20, 64),  # points' tiles
+    (128, 128, 128), (300, 136, 136), (33000, 128, 264), (66000, 128, 256),     # wide layers'
+])
+def test_point_mlp_bf16_rows_in_pieces_of_eight(M, Cin, Cout):
+    """bf16 rows on 16-byte boundaries are stored eight channels at a time: the
+    same bits as in rows off those boundaries, and nothing beside them."""
+    rng = np.random.default_rng(M + Cin + Cout)
+    x = bf16_round(rng.normal(size=(M, Cin))).astype(np.float32)
+    w = synth.kaiming_normal(rng, (Cout, Cin), Cin, bf16=True)
+    bias = rng.normal(size=Cout).astype(np.float32)
+    xd, wd = dev(x).bfloat16(), dev(w).bfloat16()
+    outs = []
+    for off in (8, 4):
+        wide = torch.full((M, Cout + 16), 7.0, dtype=torch.bfloat16, device="cuda")
+        o = wide[:, off:off + Cout]
+        pv.pvconv_point_mlp(xd, wd, bias=dev(bias), act="leaky", slope=0.2, out=o)
+        assert torch.all(wide[:, :off] == 7.0) and torch.all(wide[:, off + Cout:] == 7.0)
+        outs.append(o.contiguous())
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+    some = rng.choice(M, min(M, 500), replace=False)
+    ref = oracle.leaky_relu(oracle.linear(x[some].astype(np.float64), w, bias), 0.2)
+    assert_bf16_step(host(outs[0])[some], ref, "mlp bf16 rows")
+
+
 @pytest.mark.parametrize("B,N,R,cin,cout,xdt,odt", [
     (2, 2048, 32, 64, 128, "f32", "f32"),    # part-seg layer's end, two clouds
     (3, 777, 16, 64, 96, "bf16", "f32"),     # ragged last tile, 96 = 1.5 channel blocks
