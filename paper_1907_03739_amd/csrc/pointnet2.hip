@@ -63,17 +63,20 @@ __device__ __forceinline__ float readlane_f(float v, int l) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
 }
 // A distance as its bits: distances are >= 0, so their bits order as their
-// values, and "no point" is a negative integer.
+// values. What is not a number has bits above infinity's as an unsigned value,
+// of either sign (an infinite point's own distance is one), and so replaces
+// nothing. "No point" is a distance of 0 that stays one: it is never beyond a
+// threshold, and where 0 is the farthest, point 0 is the lowest index.
 __device__ __forceinline__ int nearer(int d, float x, float y, float z, float sx, float sy,
                                       float sz) {
-    return min(d, __float_as_int(sqdist(x, y, z, sx, sy, sz)));
+    return (int)min((uint32_t)d, __float_as_uint(sqdist(x, y, z, sx, sy, sz)));
 }
-constexpr int kFpsNoPoint = -1;
+constexpr int kFpsNoPoint = 0;
 constexpr int kFpsUnset = 0x7f800000;  // +infinity
 
-// The largest of the wave's distances, at least 0 (wave-uniform).
+// The largest of the wave's distances (wave-uniform).
 __device__ __forceinline__ int wave_farthest(int m) {
-    return (int)wave_reduce((uint32_t)max(m, 0), MaxU32{});
+    return (int)wave_reduce((uint32_t)m, MaxU32{});
 }
 
 template <int NS>
@@ -129,8 +132,7 @@ __global__ __launch_bounds__(64) void pv_fps_wave_kernel(const float* __restrict
             const uint32_t lowest = wave_reduce(low, MaxU32{});  // in every lane
             hold = __ballot(low == lowest);
         }
-        if (hold == 0ull) hold = 1ull;  // not a number: some point of the cloud
-        const int l = __ffsll((long long)hold) - 1;
+        const int l = __builtin_ctzll(hold);  // not empty: top is some lane's
         const int wk = __builtin_amdgcn_readlane(mk, l);
 #pragma unroll
         for (int k = 0; k < NS; k++)
@@ -139,7 +141,7 @@ __global__ __launch_bounds__(64) void pv_fps_wave_kernel(const float* __restrict
                 sy = readlane_f(y[k], l);
                 sz = readlane_f(z[k], l);
             }
-        pick = lane == (s & 63) ? min(l + wk * 64, N - 1) : pick;
+        pick = lane == (s & 63) ? l + wk * 64 : pick;
     }
 }
 
@@ -532,7 +534,7 @@ __global__ __launch_bounds__(NT) void pv_fps_batch_kernel(const float* __restric
             int n = 0;
 #pragma unroll
             for (int k = 0; k < PPT; k++) {
-                bool c = d[k] > T;  // no point: negative
+                bool c = d[k] > T;  // no point: 0
                 if (jmax < N) c = c && s_order[(k * NW + w) * 64 + lane] <= jmax;
                 in[k] = __ballot(c);
                 n += __popcll(in[k]);

@@ -116,6 +116,36 @@ def test_fps_at_the_edges_of_its_kernels(kind, N, npoint):
     assert np.array_equal(got, want), np.argwhere(got != want)[:5]
 
 
+def _not_numbers(N, kind, seed):
+    """A cloud with a few points that are no numbers, of either sign, and with
+    infinite ones."""
+    rng = np.random.default_rng(seed)
+    xyz = rng.uniform(-1, 1, size=(2, N, 3)).astype(np.float32)
+    bad = rng.choice(np.arange(1, N), 6, replace=False)
+    nan = np.float32(np.nan) if kind == "nan" else np.copysign(np.float32(np.nan), np.float32(-1))
+    if kind == "inf":
+        xyz[0, bad[0], 1] = np.inf
+        xyz[1, bad[1], 2] = -np.inf
+        return xyz
+    xyz[0, bad[:3], rng.integers(0, 3, 3)] = nan
+    xyz[1, 0 if kind == "first" else bad[3]] = nan
+    return xyz
+
+
+@pytest.mark.parametrize("kind", ["nan", "-nan", "first", "inf"])
+@pytest.mark.parametrize("N,npoint", [
+    (60, 20), (500, 40), (2000, 30),            # a wave, step by step
+    (1024, 200), (5000, 150), (9000, 130),      # rounds
+])
+def test_fps_of_points_that_are_not_numbers(kind, N, npoint):
+    # a distance that is no number never replaces another: such a point stays
+    # as far as at the start and is chosen from then on
+    xyz = _not_numbers(N, kind, N)
+    want = oracle.fps(xyz, npoint)
+    got = pv.pvconv_furthest_point_sample(dev(xyz), npoint, want_xyz=False).cpu().numpy()
+    assert np.array_equal(got, want), np.argwhere(got != want)[:5]
+
+
 def test_fps_is_repeatable_and_takes_one_point():
     xyz = dev(_rooms(2, 5000, 1)[0])
     a = pv.pvconv_furthest_point_sample(xyz, 400, want_xyz=False)
