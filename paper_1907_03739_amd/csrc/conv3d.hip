@@ -674,8 +674,10 @@ __global__ __launch_bounds__(256) void pv_conv_plan_kernel(
         int n = 0;
 #pragma unroll
         for (int i = 0; i < U; i++) {
-            // the exact cells lie within 1.5 of R x - 1/2 (NaN passes)
-            const float x = q[i][0] * fR, y = q[i][1] * fR, z = q[i][2] * fR;
+            // the exact cells lie within 1.5 of R x - 1/2, of R x within the
+            // grid: the border cells take what lies beyond (0: NaN)
+            auto inside = [&](float v) { return fminf(fmaxf(v * fR, 0.f), fR); };
+            const float x = inside(q[i][0]), y = inside(q[i][1]), z = inside(q[i][2]);
             const bool far = x < u0 - 2 || x > u0 + kBrick + 2 || y < v0 - 2 ||
                              y > v0 + kBrick + 2 || z < w0 - 2 || z > w0 + kBrick + 2;
             close[i] = __ballot(!far && point(j0, i) < N);

@@ -983,6 +983,49 @@ def test_forward_convolves_the_listed_voxels_alone(B, N, cin, cout, R, n_convs, 
     assert torch.equal(pv.pvconv_forward(coords, feats, layer, workspace=ws), want)
 
 
+@pytest.mark.parametrize("B,N,cin,cout,R,n_convs,devox,where", [
+    (16, 1024, 64, 64, 32, 2, "trilinear", "inside"), (16, 1023, 32, 64, 32, 2, "nearest", "inside"),
+    (8, 2048, 32, 128, 32, 1, "trilinear", "inside"), (16, 700, 16, 64, 32, 3, "trilinear", "inside"),
+    # normalised coordinates beyond the grid: the border voxels and cells take them
+    (16, 1024, 64, 64, 32, 2, "trilinear", "beyond"), (8, 1001, 32, 128, 30, 2, "trilinear", "beyond"),
+    (16, 900, 16, 64, 32, 1, "nearest", "beyond"),
+])
+def test_forward_with_given_indices_convolves_the_listed_voxels(B, N, cin, cout, R, n_convs,
+                                                                devox, where):
+    # the plan's counters are cleared by the weight packing's own launch here;
+    # the workspace holds NaN bytes, the bits are those of the separate calls
+    rng = np.random.default_rng(R + cin + n_convs)
+    L = synth.draw_pvconv(rng, cin, cout, R, n_convs, bf16=True)
+    L.devox = devox
+    layer = pv.DeviceLayer(L, "cuda", torch.bfloat16)
+    pn = synth.part_shapes(rng, B, N)
+    pn = pn / np.abs(pn).max() * 0.5 + 0.5
+    if where == "beyond":
+        pn = (pn * 1.6 - 0.3).astype(np.float32)
+        pn[:, 5, 0], pn[:, 6, 1], pn[:, 7, 2], pn[:, 8, 0] = 40.0, -1e30, np.inf, -np.inf
+    pn = pn.astype(np.float32)
+    cell = np.clip(np.floor(pn.astype(np.float64) * R), 0, R - 1).astype(np.int64)
+    ids = torch.as_tensor(((cell[..., 0] * R + cell[..., 1]) * R + cell[..., 2]).astype(np.int32),
+                          device="cuda")
+    pn = dev(pn)
+    feats = dev(rng.normal(size=(B, N, cin)).astype(np.float32))
+    size = pv.pvconv_forward_workspace_size(B, N, layer)
+    ws = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda")
+    got = pv.pvconv_forward(None, feats, layer, workspace=ws, vox_id=ids, norm=pn, ids_given=True)
+    h, _ = pv.pvconv_voxelize_from_ids(ids, feats, R, grid_dtype=torch.bfloat16)
+    for i in range(n_convs):
+        h = pv.pvconv_conv3d(h, layer.conv_w[i], R, bn=layer.conv_bn[i], act="leaky",
+                             slope=L.slope, out_dtype=torch.bfloat16)
+    dv = (pv.pvconv_devoxelize_nearest(h, R, ids) if devox == "nearest"
+          else pv.pvconv_devoxelize(h, R, pn))
+    want = pv.pvconv_point_mlp(feats, layer.mlp_w, bias=layer.mlp_b, bn=layer.mlp_bn,
+                               act="relu", residual=dv)
+    assert torch.isfinite(got).all()
+    assert torch.equal(got, want)
+    assert torch.equal(pv.pvconv_forward(None, feats, layer, workspace=ws, vox_id=ids, norm=pn,
+                                         ids_given=True), want)
+
+
 def test_forward_on_a_side_stream_and_repeatable():
     wl = synth.make_workload(2, B=2)
     layer = pv.DeviceLayer(wl.layers[0], "cuda", torch.bfloat16)
