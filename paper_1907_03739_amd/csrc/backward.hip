@@ -1002,7 +1002,10 @@ pvconv_status pv_launch_devoxelize_backward(const float* dout, int B, int N, int
 #undef PV_DEVOX_ROWS
     const int per = vec ? C / 4 : C, cells = std::max(1, 256 / per);
     const size_t groups = (ncells + cells - 1) / cells;
-    const int turns = (int)std::min<size_t>(std::max<size_t>(groups / 4096, 1), 4);
+    // up to four turns; more where four would exceed the 2^32 threads that a
+    // launch may have (64 GB and more of gradient at four bytes a cell)
+    const int turns = (int)std::max<size_t>(
+        std::min<size_t>(std::max<size_t>(groups / 4096, 1), 4), (groups >> 22) + 1);
     const unsigned gb = (unsigned)((groups + turns - 1) / turns);
 #define PV_DEVOX_BWD(VW, NEAR)                                                                   \
     hipLaunchKernelGGL((pv_devox_bwd_gather_kernel<VW, NEAR>), dim3(gb), dim3(256), 0, s, ws.srow, \

@@ -127,6 +127,27 @@ def test_devoxelize_backward_edges_and_repeatability(B, N, R, C, kind):
         assert_dot_f32(host(first), ref, mag, f"devoxelize backward (nearest={nearest})")
 
 
+def test_devoxelize_backward_of_more_cells_than_a_launch_has_threads():
+    # 2^26 cells of 129 channels, one cell a workgroup: the launch stays within
+    # 2^32 threads. One point in each cloud, at the centre of a cell: its
+    # gradient is that cell's, and every other cell's is zero.
+    B, R, C = 32, 128, 129
+    pn = torch.empty((B, 1, 3), device="cuda")
+    rng = np.random.default_rng(5)
+    cell = rng.integers(0, R, size=(B, 3))
+    cell[0], cell[-1] = 0, R - 1
+    pn.copy_(torch.as_tensor((cell[:, None] + 0.5) / R))
+    dout = torch.randn((B, 1, C), device="cuda")
+    out = torch.full((B, R ** 3, C), float("nan"), device="cuda")
+    got = pv.pvconv_devoxelize_backward(dout, R, pn, out=out)
+    for b in range(B):
+        at = int((cell[b, 0] * R + cell[b, 1]) * R + cell[b, 2])
+        assert torch.equal(got[b, at], dout[b, 0])
+        assert int(torch.count_nonzero(got[b])) == int(torch.count_nonzero(dout[b]))
+    del got, out
+    torch.cuda.empty_cache()
+
+
 def test_devoxelize_backward_unaligned_rows_and_no_points():
     B, N, R, C = 2, 400, 6, 8
     pn = _cloud("uniform", B, N, 5)
