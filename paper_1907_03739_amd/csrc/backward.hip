@@ -261,6 +261,10 @@ __global__ __launch_bounds__(64) void pv_radix_scatter_kernel(
 // set the time (2048 points, R = 32: 34 us, 8.7 us so; a bitonic network,
 // 66 dependent LDS steps, took 20.7).
 constexpr int kSortSmall = 4096;
+// 2^22 workgroups of 1024 threads are more than a launch may have: from half of
+// that on the passes' launches of 64 threads sort such clouds (of 512 points at
+// most, by the library's limit on their number).
+constexpr int kSortClouds = 1 << 21;
 
 __global__ __launch_bounds__(1024) void pv_devox_bwd_sort_kernel(
     const float* __restrict__ pn, const int32_t* __restrict__ ids, int R, int B, int N,
@@ -971,7 +975,7 @@ pvconv_status pv_launch_devoxelize_backward(const float* dout, int B, int N, int
     const size_t E = (size_t)B * N;
     const size_t ncells = (size_t)B * V;
     int cur = 0;
-    if (N <= kSortSmall) {
+    if (N <= kSortSmall && B < kSortClouds) {
         const unsigned zb = (unsigned)std::min<size_t>((ncells + 1023) / 1024, 256);
         hipLaunchKernelGGL(pv_devox_bwd_sort_kernel, dim3(B + zb), dim3(1024), 0, s, pn, ids, R, B,
                            N, ncells, ws.key[0], ws.val[0], ws.bounds, (uint32_t*)ws.act);

@@ -148,6 +148,17 @@ def test_devoxelize_backward_of_more_cells_than_a_launch_has_threads():
     torch.cuda.empty_cache()
 
 
+def test_devoxelize_backward_of_more_clouds_than_a_launch_has_threads():
+    # 2^22 clouds of one point: the one-launch sort would need 2^32 threads
+    B = (1 << 22) + 5
+    dout = torch.randn((B, 1, 1), device="cuda")
+    pn = torch.full((B, 1, 3), 0.5, device="cuda")
+    got = pv.pvconv_devoxelize_backward(dout, 1, pn)
+    assert torch.equal(got, dout)
+    ids = torch.zeros((B, 1), dtype=torch.int32, device="cuda")
+    assert torch.equal(pv.pvconv_devoxelize_nearest_backward(dout, 1, ids), dout)
+
+
 def test_devoxelize_backward_unaligned_rows_and_no_points():
     B, N, R, C = 2, 400, 6, 8
     pn = _cloud("uniform", B, N, 5)
