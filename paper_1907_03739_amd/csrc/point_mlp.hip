@@ -1000,7 +1000,8 @@ pvconv_status pv_launch_point_mlp(const void* x, bool x_bf16, int x_ld, int M, i
         // 3.5 us a call) against a thread per output (us: 2000 x 9 -> 32 3.2,
         // 8192 x 9 -> 32 4.6, 8192 x 3 -> 32 3.0, 8192 x 16 -> 32 9.7)
         const size_t total = (size_t)M * Cout;
-        if (Cin <= 8 || (Cin < 16 && total <= 131072)) {
+        // past 2^29 points the tiles' launch would exceed 2^32 threads
+        if (Cin <= 8 || (Cin < 16 && total <= 131072) || M > (1 << 29) - 32) {
             const unsigned blocks = (unsigned)((total + 255) / 256);
             if (x_bf16)
                 hipLaunchKernelGGL(pv_point_mlp_f32_elem_kernel<uint16_t>, dim3(blocks), dim3(256),

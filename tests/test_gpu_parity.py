@@ -608,6 +608,24 @@ def test_point_mlp_f32_edges_of_its_tiles(M, Cin, Cout, xdt, odt, ppc, off):
         assert_dot_f32(host(out), ref, mag, "mlp fp32")
 
 
+def test_point_mlp_f32_of_more_points_than_the_tiles_launch():
+    # 2^29 points: a tile of 32 points a workgroup would need 2^32 threads
+    M, Cin = 1 << 29, 16
+    x = torch.zeros((M, Cin), dtype=torch.bfloat16, device="cuda")
+    some = torch.tensor([0, 1, 12345, M // 2, M - 33, M - 1], device="cuda")
+    rows = torch.randint(-8, 9, (len(some), Cin), device="cuda").float()
+    x[some] = rows.bfloat16()
+    w = torch.randint(-8, 9, (1, Cin), device="cuda").float()
+    out = torch.full((M, 1), float("nan"), device="cuda")
+    pv.pvconv_point_mlp(x, w, act="none", out=out)
+    want = rows @ w.T  # small integers: exact
+    assert torch.equal(out[some], want)
+    out[some] = 0.0
+    assert int(torch.count_nonzero(out)) == 0  # NaN counts as nonzero
+    del x, out
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("M,Cin,Cout", [
     (128, 16, 8), (129, 35, 24), (160, 64, 40), (300, 64, 136), (257, 20, 64),  # points' tiles
     (128, 128, 128), (300, 136, 136), (33000, 128, 264), (66000, 128, 256),     # wide layers'
