@@ -998,10 +998,17 @@ pvconv_status pv_launch_point_mlp(const void* x, bool x_bf16, int x_ld, int M, i
     } else {
         // Few input channels: the tiles' fixed cost (operands, LDS, barrier:
         // 3.5 us a call) against a thread per output (us: 2000 x 9 -> 32 3.2,
-        // 8192 x 9 -> 32 4.6, 8192 x 3 -> 32 3.0, 8192 x 16 -> 32 9.7)
+        // 8192 x 9 -> 32 4.6, 8192 x 3 -> 32 3.0, 8192 x 16 -> 32 9.7).
+        // Few output channels: a tile computes 32, and a thread per output
+        // reads a row no more than four times (us, tiles and threads: 300000 x
+        // 9 -> 1 fp32 8.5, 4.9, -> 4 11.4, 8.8; 10 -> 4 11.4, 9.7, but 11 -> 3
+        // 10.6, 14.3; 13 -> 1 8.9, 8.3, but 15 -> 1 9.3, 10.2; bf16 15 -> 1
+        // 9.9, 6.5, 16 -> 1 7.9, 11.3).
         const size_t total = (size_t)M * Cout;
+        const bool few = Cin <= 8 || (Cin < 16 && total <= 131072) ||
+                         (Cin <= 10 && Cout <= 4) || (Cin < (x_bf16 ? 16 : 14) && Cout == 1);
         // past 2^29 points the tiles' launch would exceed 2^32 threads
-        if (Cin <= 8 || (Cin < 16 && total <= 131072) || M > (1 << 29) - 32) {
+        if (few || M > (1 << 29) - 32) {
             const unsigned blocks = (unsigned)((total + 255) / 256);
             if (x_bf16)
                 hipLaunchKernelGGL(pv_point_mlp_f32_elem_kernel<uint16_t>, dim3(blocks), dim3(256),

@@ -577,6 +577,10 @@ def test_point_mlp_f32_matches_oracle(M, Cin, Cout):
     # a thread per output: few input channels, and its last size
     (31, 4, 33, "f32", "f32", 0, 0), (4096, 12, 32, "bf16", "f32", 0, 0),
     (4097, 12, 32, "f32", "f32", 0, 0), (64, 36, 64, "bf16", "f32", 32, 0),
+    # many points and few outputs: threads, and the tiles beside them
+    (40000, 10, 4, "f32", "f32", 0, 0), (40000, 11, 4, "f32", "f32", 0, 0),
+    (140001, 13, 1, "f32", "f32", 0, 0), (140001, 14, 1, "f32", "bf16", 0, 0),
+    (140001, 15, 1, "bf16", "f32", 0, 1), (140001, 16, 1, "bf16", "f32", 0, 0),
     (500, 130, 70, "f32", "f32", 250, 0), (257, 1000, 40, "f32", "f32", 0, 0),
     (100, 64, 32, "f32", "f32", 0, 1),     # rows off 16-byte boundaries
     (100, 64, 32, "bf16", "f32", 0, 1), (96, 20, 8, "bf16", "bf16", 0, 4),
