@@ -961,6 +961,13 @@ unsigned grid_for(size_t total) {
 
 }  // namespace
 
+// N lies in the upper half of the doubling that holds it, up to 8192.
+static bool fps_upper_half(int N) {
+    int top = 1024;
+    while (top < N) top *= 2;
+    return top <= 8192 && N > top / 4 * 3;
+}
+
 pvconv_status pv_launch_fps(const float* xyz, int B, int N, int npoint, int32_t* idx,
                             float* new_xyz, hipStream_t s) {
     if (B == 0) return PVCONV_OK;
@@ -974,8 +981,14 @@ pvconv_status pv_launch_fps(const float* xyz, int B, int N, int npoint, int32_t*
     // The rounds cost a sort (~10 us) and yield one to three samples each at
     // first: up to 64 samples the plain steps are as fast or faster (us, four
     // clouds: 8192 -> 32 points 39 against 68, -> 64 points 72 against 84,
-    // -> 1024 points 1080 against 365).
-    else if (npoint <= 64) {
+    // -> 1024 points 1080 against 365). A step costs what the cloud's size
+    // rounded up to a power of two does, the rounds grow with the cloud: in the
+    // upper half of each doubling up to 8192 points the steps hold to 72
+    // samples (us, steps and rounds, four to 64 clouds: 1024 -> 65 38 and 41 to
+    // 46, -> 80 46 and 43 to 52; 8192 -> 65 74 and 80 to 91, -> 80 90 and 84 to
+    // 99; but 1025 -> 65 43 and 38, 4097 -> 80 88 and 79). Clouds of few
+    // distinct points (one in eight) would cross at 130.
+    else if (npoint <= (fps_upper_half(N) ? 72 : 64)) {
         if (N <= 1024) PV_FPS(256, pv_fps_step_kernel<4, 256, true>);
         else if (N <= 2048) PV_FPS(256, pv_fps_step_kernel<8, 256, true>);
         else if (N <= 4096) PV_FPS(256, pv_fps_step_kernel<16, 256, true>);

@@ -108,6 +108,9 @@ def _edge_cloud(kind, N):
     # few samples: step by step
     ("lattice", 600, 64), ("lattice", 2000, 33), ("outlier", 4096, 64), ("tiny", 8192, 64),
     ("lattice", 9000, 50),
+    # the last such number, and one more
+    ("lattice", 1024, 72), ("line", 4000, 72), ("lattice", 8192, 73), ("outlier", 6145, 72),
+    ("lattice", 6144, 65), ("tiny", 768, 65), ("lattice", 16384, 65),
 ])
 def test_fps_at_the_edges_of_its_kernels(kind, N, npoint):
     xyz = _edge_cloud(kind, N)
