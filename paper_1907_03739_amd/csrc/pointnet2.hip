@@ -927,8 +927,8 @@ __global__ __launch_bounds__(256) void pv_three_interpolate_kernel(
 // Maximum over each group's S rows (a centre's neighbours after the shared
 // MLP): out[g][c] = max_k x[g*S + k][c]. V consecutive channels per thread,
 // channels fastest; exact, so the order of the comparisons does not matter.
-// With V = 8 a thread streams 16-byte pieces (4096 groups of 32 x 64 bf16:
-// 12 us one by one, 5.6 with 8).
+// Eight rows are in flight a thread (4096 groups of 32 x 64 bf16: 6.2 us one
+// row after the other, 3.2 so). V = 8 where that leaves threads enough.
 // ---------------------------------------------------------------------------
 template <typename XT, typename OT, int V>
 __global__ __launch_bounds__(256) void pv_group_max_kernel(const XT* __restrict__ x, int x_ld,
@@ -1073,7 +1073,14 @@ pvconv_status pv_launch_three_interpolate(const void* feats, bool feat_bf16, int
 pvconv_status pv_launch_group_max(const void* x, bool x_bf16, int x_ld, int G, int S, int C,
                                   void* out, bool out_bf16, int out_ld, hipStream_t s) {
     if ((size_t)G * C == 0) return PVCONV_OK;
-    const bool vec = rows_vec8(x, x_ld, C, x_bf16) && rows_vec8(out, out_ld, C, out_bf16);
+    // A thread walks S rows one group of loads after the other, so the threads
+    // in flight set the time: eight channels a thread pay from 2^19 outputs on
+    // (us, eight and one: bf16, 32 rows of 64, 4096 groups 3.4 and 3.2, 8192
+    // 4.9 and 5.0; 8 rows of 32, 32768 groups 2.8 and 3.9; 2048 rows of 1024,
+    // 4 groups 156 and 44), fp32 rows of as many bytes only up to 8 of them (8
+    // rows of 32, 32768 groups 4.3 and 5.3; 32 of 128, 4096 13.6 and 11.2).
+    const bool vec = rows_vec8(x, x_ld, C, x_bf16) && rows_vec8(out, out_ld, C, out_bf16) &&
+                     (size_t)G * C >= (1u << 19) && (x_bf16 || S <= 8);
     const size_t total = (size_t)G * (vec ? C / 8 : C);
 #define PV_GMAX(XT, OT, V)                                                                  \
     hipLaunchKernelGGL((pv_group_max_kernel<XT, OT, V>), dim3(grid_for(total)), dim3(256), 0, s, \

@@ -279,6 +279,28 @@ def test_three_interpolate_into_a_column_slice():
 
 @pytest.mark.parametrize("fdt", ["f32", "bf16"])
 @pytest.mark.parametrize("odt", ["f32", "bf16"])
+@pytest.mark.parametrize("G,S,C", [
+    # either side of eight channels a thread: the number of outputs, of rows
+    # (fp32), whole groups of eight
+    (16384, 8, 32), (16383, 8, 32), (16384, 9, 32), (65536, 1, 8), (8192, 3, 72), (40000, 2, 13),
+])
+def test_group_max_by_eight_channels_and_one_by_one(G, S, C, fdt, odt):
+    # rows off 16-byte boundaries are taken one by one: the same values, and
+    # nothing is written beside them
+    tdt = {"f32": torch.float32, "bf16": torch.bfloat16}
+    x = torch.randn((G * S, C), device="cuda").to(tdt[fdt])
+    want = x.view(G, S, C).amax(1).to(tdt[odt])
+    for off in (8, 1):
+        wide = torch.full((G * S, C + 16), float("inf"), dtype=tdt[fdt], device="cuda")
+        wide[:, off:off + C] = x
+        out = torch.full((G, C + 16), 7.0, dtype=tdt[odt], device="cuda")
+        pv.pvconv_group_max(wide[:, off:off + C], S, out=out[:, off:off + C])
+        assert torch.equal(out[:, off:off + C], want)
+        assert bool((out[:, :off] == 7).all()) and bool((out[:, off + C:] == 7).all())
+
+
+@pytest.mark.parametrize("fdt", ["f32", "bf16"])
+@pytest.mark.parametrize("odt", ["f32", "bf16"])
 @pytest.mark.parametrize("C,nsample", [(8, 1), (64, 32), (40, 5), (13, 7), (5, 3)])
 def test_rows_in_pieces_of_eight_are_the_rows_one_by_one(C, nsample, fdt, odt):
     # grouping, interpolation and the neighbour maximum take eight channels at
