@@ -895,7 +895,8 @@ __global__ __launch_bounds__(kNnThreads) void pv_three_nn_kernel(
 // Inverse-distance interpolation: out[b][i][c] = sum_k w[b][i][k] *
 // feats[b][idx[b][i][k]][c], V consecutive channels per thread, channels
 // fastest. V = 8 where C, the row strides and the alignments allow 16-byte
-// loads (4 x 8192 points of 128 channels: 16.6 us one by one, 6.0 with 8).
+// loads (4 x 8192 points of 128 channels: 16.6 us one by one, 6.0 with 8) and
+// that leaves threads enough.
 // ---------------------------------------------------------------------------
 template <typename FT, typename OT, int V>
 __global__ __launch_bounds__(256) void pv_three_interpolate_kernel(
@@ -1051,7 +1052,12 @@ pvconv_status pv_launch_three_interpolate(const void* feats, bool feat_bf16, int
                                           int n, void* out, bool out_bf16, int out_ld,
                                           hipStream_t s) {
     if ((size_t)B * n * C == 0) return PVCONV_OK;
-    const bool vec = rows_vec8(feats, feat_ld, C, feat_bf16) && rows_vec8(out, out_ld, C, out_bf16);
+    // From 250000 outputs on: by eight that is half a wave a SIMD, and with fewer
+    // the wide loads do not make up for the waves (us, one by one and by eight:
+    // 4 x 256 points of 64 channels 2.31 and 2.41, of 128 2.36 and 2.45, of 256
+    // 2.74 and 2.56; 500 of 512 2.73 and 2.60; 4 x 8192 of 8 2.75 and 2.76).
+    const bool vec = rows_vec8(feats, feat_ld, C, feat_bf16) &&
+                     rows_vec8(out, out_ld, C, out_bf16) && (size_t)B * n * C >= 250000;
     const size_t total = (size_t)B * n * (vec ? C / 8 : C);
 #define PV_INTERP(FT, OT, V)                                                                \
     hipLaunchKernelGGL((pv_three_interpolate_kernel<FT, OT, V>), dim3(grid_for(total)),      \

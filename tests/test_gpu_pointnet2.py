@@ -301,6 +301,35 @@ def test_group_max_by_eight_channels_and_one_by_one(G, S, C, fdt, odt):
 
 @pytest.mark.parametrize("fdt", ["f32", "bf16"])
 @pytest.mark.parametrize("odt", ["f32", "bf16"])
+@pytest.mark.parametrize("n,C", [(977, 64), (976, 64), (8192, 8), (930, 72), (6000, 13)])
+def test_three_interpolate_by_eight_channels_and_one_by_one(n, C, fdt, odt):
+    # either side of eight channels a thread (250000 outputs); rows off 16-byte
+    # boundaries are taken one by one: the same bits, nothing beside them
+    tdt = {"f32": torch.float32, "bf16": torch.bfloat16}
+    B, m = 4, 100
+    xyz = dev(_rooms(B, n, C)[0])
+    idx, w = pv.pvconv_three_nn(xyz, xyz[:, :m].contiguous())
+    src = torch.randn((B, m, C), device="cuda").to(tdt[fdt])
+    ref = oracle.three_interpolate(src.float().cpu().numpy(), idx.cpu().numpy(), w.cpu().numpy())
+    got = []
+    for off in (8, 1):
+        wide = torch.zeros((B, m, C + 16), dtype=tdt[fdt], device="cuda")
+        wide[:, :, off:off + C] = src
+        out = torch.full((B, n, C + 16), 7.0, dtype=tdt[odt], device="cuda")
+        pv.pvconv_three_interpolate(wide[:, :, off:off + C], idx, w, out=out[:, :, off:off + C])
+        assert bool((out[:, :, :off] == 7).all()) and bool((out[:, :, off + C:] == 7).all())
+        got.append(out[:, :, off:off + C].contiguous())
+    assert torch.equal(*got)
+    if odt == "bf16":
+        assert_bf16_step(host(got[0]), ref, "interpolation")
+    else:
+        mag = oracle.three_interpolate(np.abs(src.float().cpu().numpy()), idx.cpu().numpy(),
+                                       np.abs(w.cpu().numpy()))
+        assert np.all(np.abs(host(got[0]) - ref) <= 4 * 2.0 ** -24 * mag + 1e-30)
+
+
+@pytest.mark.parametrize("fdt", ["f32", "bf16"])
+@pytest.mark.parametrize("odt", ["f32", "bf16"])
 @pytest.mark.parametrize("C,nsample", [(8, 1), (64, 32), (40, 5), (13, 7), (5, 3)])
 def test_rows_in_pieces_of_eight_are_the_rows_one_by_one(C, nsample, fdt, odt):
     # grouping, interpolation and the neighbour maximum take eight channels at
