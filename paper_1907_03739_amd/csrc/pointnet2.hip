@@ -742,7 +742,7 @@ bool rows_vec8(const void* p, int ld, int C, bool bf16) {
 // per thread, elements fastest. V = 8 (output rows at 16-byte boundaries):
 // one index and one store for eight elements, read one by one (a row's
 // features start three elements in, off any boundary): 131072 rows of 3 + 32
-// bf16 18.8 us one by one, 11.2 with 8. A row's last piece is written element
+// bf16 16.9 us one by one, 11.3 with 8. A row's last piece is written element
 // by element: what follows the row is not the kernel's.
 // ---------------------------------------------------------------------------
 template <typename FT, typename OT, int V>
@@ -756,7 +756,7 @@ __global__ __launch_bounds__(256) void pv_group_kernel(
         const size_t row = e / G;
         const int c0 = (int)(e - row * G) * V;
         const size_t q = row / nsample;
-        const size_t p = (q / M) * N + min(max(idx[row], 0), N - 1);
+        const size_t p = (size_t)(int)(q / M) * N + min(max(idx[row], 0), N - 1);
         float v[V];
 #pragma unroll
         for (int t = 0; t < V; t++) {
@@ -1020,7 +1020,15 @@ pvconv_status pv_launch_group(const float* xyz, const void* feats, bool feat_bf1
                               const int32_t* idx, int nsample, void* out, bool out_bf16,
                               int out_ld, hipStream_t s) {
     if ((size_t)B * M * nsample == 0) return PVCONV_OK;
-    const bool vec = pv_aligned16(out) && ((size_t)out_ld * (out_bf16 ? 2 : 4)) % 16 == 0;
+    // Eight elements a thread from 24 channels on (narrower rows are mostly their
+    // ragged last piece) and where that leaves threads enough (us, one by one
+    // and by eight, bf16: 131072 rows of 3 + 5 5.2 and 5.8, + 16 10.0 and 10.1,
+    // + 20 11.4 and 12.6, + 24 13.3 and 11.9, + 64 31 and 14.5; 512 rows of + 64
+    // 2.6 and 3.4; 8192 rows of + 32 3.2 and 3.6, + 64 4.0 and 3.7; fp32 8192
+    // rows of + 64 3.9 and 4.1, 32768 of + 24 5.2 and 5.1).
+    const size_t values = (size_t)B * M * nsample * C;
+    const bool vec = pv_aligned16(out) && ((size_t)out_ld * (out_bf16 ? 2 : 4)) % 16 == 0 &&
+                     C >= 24 && values >= (out_bf16 ? 2u << 18 : 3u << 18);
     const size_t total = (size_t)B * M * nsample * (vec ? (3 + C + 7) / 8 : 3 + C);
 #define PV_GROUP(FT, OT, V)                                                                  \
     hipLaunchKernelGGL((pv_group_kernel<FT, OT, V>), dim3(grid_for(total)), dim3(256), 0, s,    \

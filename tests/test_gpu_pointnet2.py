@@ -330,48 +330,33 @@ def test_three_interpolate_by_eight_channels_and_one_by_one(n, C, fdt, odt):
 
 @pytest.mark.parametrize("fdt", ["f32", "bf16"])
 @pytest.mark.parametrize("odt", ["f32", "bf16"])
-@pytest.mark.parametrize("C,nsample", [(8, 1), (64, 32), (40, 5), (13, 7), (5, 3)])
-def test_rows_in_pieces_of_eight_are_the_rows_one_by_one(C, nsample, fdt, odt):
-    # grouping, interpolation and the neighbour maximum take eight channels at
-    # once where the rows are aligned; rows shifted off 16 bytes take the
-    # element-wise forms, and the bits are the same. Nothing is written beside
-    # the rows.
+@pytest.mark.parametrize("M,C,nsample", [
+    # rows of whole pieces of eight and rows with a ragged last one; either
+    # side of the fewest channels and of the fewest values
+    (1024, 24, 32), (1024, 23, 32), (512, 29, 32), (600, 61, 12), (300, 64, 20), (100, 64, 20),
+    (400, 128, 8), (33, 5, 3),
+])
+def test_group_points_by_eight_elements_and_one_by_one(M, C, nsample, fdt, odt):
+    # rows whose places start at 16-byte boundaries are written eight elements
+    # at once, rows off them one by one: the same bits, nothing beside them
     tdt = {"f32": torch.float32, "bf16": torch.bfloat16}
-    B, N, M = 3, 150, 33
+    B, N = 2, 1500
     xyz = dev(_rooms(B, N, C)[0])
     rng = np.random.default_rng(C)
     centers = xyz[:, :M].contiguous()
     idx = torch.as_tensor(rng.integers(0, N, size=(B, M, nsample)), dtype=torch.int32).cuda()
-    wide = torch.zeros((B, N, C + 16), dtype=tdt[fdt], device="cuda")
-    src = dev(rng.normal(size=(B, N, C)).astype(np.float32)).to(tdt[fdt])
-
-    def rows(off):
-        wide[:, :, off:off + C] = src
-        return wide[:, :, off:off + C]
-
-    def outs(shape, off, width):
-        buf = torch.full(shape + (width + 32,), 7.0, dtype=tdt[odt], device="cuda")
-        return buf, buf[..., off:off + width]
-
-    def beside(buf, off, width):
-        return bool((buf[..., :off] == 7).all()) and bool((buf[..., off + width:] == 7).all())
-
-    nn_idx, nn_w = pv.pvconv_three_nn(xyz, centers)
-    deep = src[:, :M]
+    feats = torch.randn((B, N, C), device="cuda").to(tdt[fdt])
+    W = 3 + C
+    width = (W + 7) // 8 * 8 + 16
     got = []
     for off in (8, 1):
-        buf, o = outs((B, M, nsample), off, 3 + C)
-        pv.pvconv_group_points(xyz, rows(off), centers, idx, out=o)
-        assert beside(buf, off, 3 + C)
-        buf2, o2 = outs((B, N), off, C)
-        wide[:, :M, off:off + C] = deep
-        pv.pvconv_three_interpolate(wide[:, :M, off:off + C].contiguous() if off == 8 else
-                                    deep.contiguous(), nn_idx, nn_w, out=o2)
-        assert beside(buf2, off, C)
-        r = rows(off).reshape(B * N, C) if off == 8 else src.reshape(B * N, C).contiguous()
-        buf3, o3 = outs((B * 50,), off, C)
-        pv.pvconv_group_max(r, 3, out=o3)
-        assert beside(buf3, off, C)
-        got.append((o.clone(), o2.clone(), o3.clone()))
-    for a, b in zip(*got):
-        assert torch.equal(a, b)
+        wide = torch.full((B * M * nsample, width), 7.0, dtype=tdt[odt], device="cuda")
+        pv.pvconv_group_points(xyz, feats, centers, idx, out=wide[:, off:off + W])
+        assert bool((wide[:, :off] == 7).all()) and bool((wide[:, off + W:] == 7).all())
+        got.append(wide[:, off:off + W].contiguous())
+    assert torch.equal(*got)
+    at = idx.long().view(B, -1)
+    rel = torch.stack([xyz[b][at[b]] - centers[b].repeat_interleave(nsample, 0)
+                       for b in range(B)]).view(-1, 3)
+    rows = torch.stack([feats[b][at[b]] for b in range(B)]).view(-1, C)
+    assert torch.equal(got[0], torch.cat([rel.to(tdt[odt]), rows.to(tdt[odt])], 1))
