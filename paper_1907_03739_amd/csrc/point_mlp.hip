@@ -26,14 +26,13 @@ namespace {
 
 constexpr int kWaves = 4;
 
-// out_bf16 where rows of eight channels are whole 16-byte pieces of the output.
+// bf16 outputs where rows of eight channels are whole 16-byte pieces of the output.
 // Lanes l and l + 32 hold channels 8g .. 8g+3 and 8g+4 .. 8g+7 of one point;
 // the halves swapped, lane l has all of group g (a) and lane l + 32 all of the
 // next (b), and a store writes 32 bytes of a row rather than 16: the stores of
 // all workgroups go out at once and the number of row pieces they touch is what
 // they wait for (16384 x 512 -> 2048: 58 us with 8-byte stores, 49 with 16;
 // 131072 x 35 -> 32 -> 32 -> 64: 29.2, 26.0).
-constexpr int kBf16Rows8 = 2;
 __device__ __forceinline__ uint4 swap_rows8(const float4& a, const float4& b) {
     const auto lo = __builtin_amdgcn_permlane32_swap(pv_pack_bf16x2(a.x, a.y),
                                                      pv_pack_bf16x2(b.x, b.y), false, false);
@@ -125,7 +124,12 @@ struct RawOf<uint16_t> {
 // more waves gathering while the GEMM waves load and multiply measured
 // slower: two waves per SIMD leave room for only two items' loads in flight.)
 // Requires C4, Cout % 8 == 0 and a 16-byte aligned grid.
-template <int NB, typename XT, bool VEC, bool C4, bool DV = false>
+//
+// ROWS8 (with C4): the output is bf16 rows that bf16_rows8 allows. A kernel of
+// its own: as a branch on an argument it cost the other outputs 0.3 us a call
+// (fp32 rows of 2048 x 64 -> 128 7.3 us, 6.9 apart; 1000 x 32 -> 32 3.7, 3.35)
+// and its own as much (bf16 6.4, 5.9; 3.4, 3.2).
+template <int NB, typename XT, bool VEC, bool C4, bool DV = false, bool ROWS8 = false>
 __global__ __launch_bounds__(kWaves * 64) void pv_point_mlp_tile_kernel(
     const XT* __restrict__ x, int x_ld, int M, int Cin, int Cout, const uint16_t* __restrict__ w,
     PvBnFold bn, int act, float slope, const float* __restrict__ cloud_bias, int ppc,
@@ -330,18 +334,17 @@ __global__ __launch_bounds__(kWaves * 64) void pv_point_mlp_tile_kernel(
             res[nb][g].w += v[3];
         }
     const size_t orow = (size_t)(m0 + r32) * out_ld;
-    if constexpr (C4) {
-        if (out_bf16 == kBf16Rows8) {
+    if constexpr (ROWS8) {
+        static_assert(C4, "whole pieces of eight channels");
 #pragma unroll
-            for (int nb = 0; nb < NB; nb++)
+        for (int nb = 0; nb < NB; nb++)
 #pragma unroll
-                for (int g = 0; g < 4; g += 2) {
-                    const uint4 o = swap_rows8(res[nb][g], res[nb][g + 1]);
-                    const int c = nb * 32 + (g + h) * 8;
-                    if (mrow && c < ncols) *(uint4*)((uint16_t*)out + orow + n0 + c) = o;
-                }
-            return;
-        }
+            for (int g = 0; g < 4; g += 2) {
+                const uint4 o = swap_rows8(res[nb][g], res[nb][g + 1]);
+                const int c = nb * 32 + (g + h) * 8;
+                if (mrow && c < ncols) *(uint4*)((uint16_t*)out + orow + n0 + c) = o;
+            }
+        return;
     }
     if (!mrow) return;
 #pragma unroll
@@ -404,8 +407,9 @@ __device__ __forceinline__ uint4 piece_bf16(const float* p) {
 // weight rows 16-byte aligned, residual / cloud rows 16-byte aligned, output
 // rows 16-byte (fp32) or 8-byte (bf16) aligned.
 // EXT: a per-cloud row or a residual is given (else neither is read, and
-// the registers that prefetch them are not needed).
-template <int NB, int MB, int WN, int WM, typename XT, bool EXT>
+// the registers that prefetch them are not needed). ROWS8: as in
+// the tile kernel.
+template <int NB, int MB, int WN, int WM, typename XT, bool EXT, bool ROWS8>
 __global__ __launch_bounds__(64 * WN * WM, 1) void pv_point_mlp_lds_kernel(
     const XT* __restrict__ x, int x_ld, int M, int Cin, int Cout, const uint16_t* __restrict__ w,
     PvBnFold bn, int act, float slope, const float* __restrict__ cloud_bias, int ppc,
@@ -562,7 +566,7 @@ __global__ __launch_bounds__(64 * WN * WM, 1) void pv_point_mlp_lds_kernel(
                 val[g] = float4{v[0] + rs.x, v[1] + rs.y, v[2] + rs.z, v[3] + rs.w};
             }
             if (blk + 1 < MB * NB) load_ext((blk + 1) / NB, (blk + 1) % NB);
-            if (out_bf16 == kBf16Rows8) {
+            if constexpr (ROWS8) {
 #pragma unroll
                 for (int g = 0; g < 4; g += 2) {
                     const uint4 o = swap_rows8(val[g], val[g + 1]);
@@ -713,9 +717,11 @@ __global__ __launch_bounds__(256) void pv_point_mlp_f32_elem_kernel(
         ((float*)out)[m * out_ld + n] = v;
 }
 
-int out_kind(const void* out, bool out_bf16, int out_ld, int Cout) {
-    if (!out_bf16) return 0;
-    return Cout % 8 == 0 && out_ld % 8 == 0 && pv_aligned16(out) ? kBf16Rows8 : 1;
+// From 24 channels on: a tile's lanes past the last channel have nothing to
+// store but take part in the swaps (8192 x 64 -> 8 3.2 us with 8-byte stores,
+// 3.3 with 16, -> 24 3.5 with either, -> 64 4.6, 4.2).
+bool bf16_rows8(const void* out, bool out_bf16, int out_ld, int Cout) {
+    return out_bf16 && Cout >= 24 && Cout % 8 == 0 && out_ld % 8 == 0 && pv_aligned16(out);
 }
 
 template <int NB, typename XT>
@@ -724,15 +730,20 @@ void launch_mfma(const void* x, int x_ld, int M, int Cin, int Cout, const void* 
                  const float* res, int res_ld, void* out, bool out_bf16, int out_ld,
                  hipStream_t s) {
     dim3 g((M + kWaves * 32 - 1) / (kWaves * 32), (Cout + NB * 32 - 1) / (NB * 32));
-#define PV_TILE(V, C)                                                                         \
-    hipLaunchKernelGGL((pv_point_mlp_tile_kernel<NB, XT, V, C>), g, dim3(kWaves * 64), 0, s, \
-                       (const XT*)x, x_ld, M, Cin, Cout, (const uint16_t*)w, bn, act, slope,   \
-                       cb, ppc, res, res_ld, out, out_kind(out, out_bf16, out_ld, Cout),       \
-                       out_ld, PvDevoxIn{})
+#define PV_TILE(V, C, R8)                                                                     \
+    hipLaunchKernelGGL((pv_point_mlp_tile_kernel<NB, XT, V, C, false, R8>), g,                 \
+                       dim3(kWaves * 64), 0, s, (const XT*)x, x_ld, M, Cin, Cout,              \
+                       (const uint16_t*)w, bn, act, slope, cb, ppc, res, res_ld, out,          \
+                       (int)out_bf16, out_ld, PvDevoxIn{})
+    const bool rows8 = c4 && bf16_rows8(out, out_bf16, out_ld, Cout);
     if (vec) {
-        if (c4) PV_TILE(true, true); else PV_TILE(true, false);
+        if (rows8) PV_TILE(true, true, true);
+        else if (c4) PV_TILE(true, true, false);
+        else PV_TILE(true, false, false);
     } else {
-        if (c4) PV_TILE(false, true); else PV_TILE(false, false);
+        if (rows8) PV_TILE(false, true, true);
+        else if (c4) PV_TILE(false, true, false);
+        else PV_TILE(false, false, false);
     }
 #undef PV_TILE
 }
@@ -745,16 +756,17 @@ void launch_lds(const void* x, int x_ld, int M, int Cin, int Cout, const void* w
     typedef GemmShape<NB, MB, WN, WM> S;
     const int ntn = (Cout + S::TN - 1) / S::TN;
     const int nblocks = ntn * ((M + S::TM - 1) / S::TM);
-    if (cb || res)
-        hipLaunchKernelGGL((pv_point_mlp_lds_kernel<NB, MB, WN, WM, XT, true>), dim3(nblocks),
-                           dim3(S::NTHR), 0, s, (const XT*)x, x_ld, M, Cin, Cout, (const uint16_t*)w,
-                           bn, act, slope, cb, ppc, res, res_ld, out,
-                           out_kind(out, out_bf16, out_ld, Cout), out_ld, ntn, nblocks);
-    else
-        hipLaunchKernelGGL((pv_point_mlp_lds_kernel<NB, MB, WN, WM, XT, false>), dim3(nblocks),
-                           dim3(S::NTHR), 0, s, (const XT*)x, x_ld, M, Cin, Cout, (const uint16_t*)w,
-                           bn, act, slope, cb, ppc, res, res_ld, out,
-                           out_kind(out, out_bf16, out_ld, Cout), out_ld, ntn, nblocks);
+#define PV_LDS(EXT, R8)                                                                        \
+    hipLaunchKernelGGL((pv_point_mlp_lds_kernel<NB, MB, WN, WM, XT, EXT, R8>), dim3(nblocks),   \
+                       dim3(S::NTHR), 0, s, (const XT*)x, x_ld, M, Cin, Cout,                  \
+                       (const uint16_t*)w, bn, act, slope, cb, ppc, res, res_ld, out,          \
+                       (int)out_bf16, out_ld, ntn, nblocks)
+    if (bf16_rows8(out, out_bf16, out_ld, Cout)) {
+        if (cb || res) PV_LDS(true, true); else PV_LDS(false, true);
+    } else {
+        if (cb || res) PV_LDS(true, false); else PV_LDS(false, false);
+    }
+#undef PV_LDS
 }
 
 // ---- small-M path --------------------------------------------------------
@@ -1052,13 +1064,17 @@ pvconv_status pv_launch_devox_point_mlp(const PvDevoxIn& dv, const void* x, bool
     // 64-channel tiles also for wider layers: twice the workgroups (two per
     // CU at the part-seg shape) to cover the gather's latency, 1 % faster on
     // that layer than 128-channel tiles, though the point rows are read twice
-#define PV_DV(NB, XT)                                                                         \
-    hipLaunchKernelGGL((pv_point_mlp_tile_kernel<NB, XT, true, true, true>),                  \
+#define PV_DV(NB, XT, R8)                                                                     \
+    hipLaunchKernelGGL((pv_point_mlp_tile_kernel<NB, XT, true, true, true, R8>),              \
                        dim3((M + kWaves * 32 - 1) / (kWaves * 32), (Cout + NB * 32 - 1) / (NB * 32)), \
                        dim3(kWaves * 64), 0, s, (const XT*)x, x_ld, M, Cin, Cout,              \
                        (const uint16_t*)w, bn, act, slope, nullptr, 1, nullptr, 0, out,         \
-                       out_kind(out, out_bf16, out_ld, Cout), out_ld, dv)
-    if (x_bf16) PV_DV(2, uint16_t); else PV_DV(2, float);
+                       (int)out_bf16, out_ld, dv)
+    if (bf16_rows8(out, out_bf16, out_ld, Cout)) {
+        if (x_bf16) PV_DV(2, uint16_t, true); else PV_DV(2, float, true);
+    } else {
+        if (x_bf16) PV_DV(2, uint16_t, false); else PV_DV(2, float, false);
+    }
 #undef PV_DV
     return pv_launch_status();
 }
