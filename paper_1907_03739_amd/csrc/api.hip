@@ -610,7 +610,7 @@ pvconv_status pvconv_forward_ex(const float* coords, const void* feats, pvconv_d
     // output is also computed only there, and constant elsewhere.
     if (rows) {
         st = pv_launch_conv_plan(w.plan, w.counts, pnorm, L->devox == PVCONV_DEVOX_NEAREST, B, N,
-                                 R, L->cout, s);
+                                 R, L->n_convs == 1 ? L->cin : L->cout, L->cout, s);
         if (st != PVCONV_OK) return st;
     }
     for (int i = 0; i < L->n_convs; i++) {

@@ -1455,15 +1455,24 @@ PvConvPlan pv_conv_plan_carve(void* base, int B, int R, size_t* bytes) {
 }
 
 pvconv_status pv_launch_conv_plan(PvConvPlan& plan, const int32_t* counts, const float* pn,
-                                  bool nearest, int B, int N, int R, int Cout, hipStream_t s) {
+                                  bool nearest, int B, int N, int R, int Cin, int Cout,
+                                  hipStream_t s) {
     const int nbr = (R + kBrick - 1) / kBrick;
     const int nb3 = nbr * nbr * nbr;
-    // Every brick's workgroup reads its cloud's points: 2.1 M of them (16
-    // clouds of 2048 points, 64 bricks each) cost 9 of the plan's 14.5 us and
-    // save a third of the last convolution's MFMAs. Past four times that, and
-    // on small grids, the last convolution computes D1.
+    // Every brick's workgroup reads its cloud's points, 2048 a turn of 2.5 us:
+    // 2.1 M of them (16 clouds of 2048 points, 64 bricks each) cost 9 of the
+    // plan's 14.5 us and save a third of the last convolution's MFMAs. Past
+    // four times that, on small grids, and where the convolution has few
+    // channels for the points (Cin x Cout below 2 N), the last convolution
+    // computes D1 (us a layer, the voxels read and D1, Cin x Cout / N in
+    // brackets: 8 clouds of 16384 points, 64 -> 64 twice, R = 32 [0.25] 187 and
+    // 156; 4 of 16384, 64 -> 128 once [0.5] 141 and 115; 8 of 8192, 64 -> 128
+    // once [1] 133 and 125; 16 of 5000, 64 -> 128 once [1.6] 161 and 158; 64 of
+    // 2048, 64 -> 64 twice [2] 332 and 348; 16 of 2048, 64 -> 128 twice [8] 181
+    // and 196, 64 -> 256 twice [32] 411 and 504).
     const bool small = rows_small(B, R, Cout);
-    if (nearest || (long long)B * nb3 * N > (8ll << 20)) pn = nullptr;
+    if (nearest || (long long)B * nb3 * N > (8ll << 20) || (long long)Cin * Cout < 2ll * N)
+        pn = nullptr;
     if (small || (!nearest && !pn)) plan.list[1] = nullptr;
     if (!small)
         hipLaunchKernelGGL(pv_conv_plan_kernel, dim3(B * nb3), dim3(256), 0, s, counts, pn, N,

@@ -204,9 +204,11 @@ struct PvConvPlan {
 // The plan's arrays in a workspace (256-byte aligned) of *bytes.
 PvConvPlan pv_conv_plan_carve(void* base, int B, int R, size_t* bytes);
 // counts [B][R^3]: the points per voxel; pn [B][N][3]: their normalised
-// coordinates, at whose corner cells (nearest: voxels) the grid is read.
+// coordinates, at whose corner cells (nearest: voxels) the grid is read. Cin,
+// Cout: the last convolution's channels.
 pvconv_status pv_launch_conv_plan(PvConvPlan& plan, const int32_t* counts, const float* pn,
-                                  bool nearest, int B, int N, int R, int Cout, hipStream_t s);
+                                  bool nearest, int B, int N, int R, int Cin, int Cout,
+                                  hipStream_t s);
 // A convolution inside a layer's forward that computes the voxels of one of
 // the plan's lists (bf16 grids, packed weights).
 struct PvConvRows {

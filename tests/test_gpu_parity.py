@@ -975,6 +975,10 @@ def _list_cloud(kind, B, N):
     (5, 777, 9, 64, 16, 2, "trilinear", "cube"),
     (5, 600, 64, 128, 17, 3, "nearest", "shapes"),
     (64, 3, 8, 8, 1, 2, "trilinear", "cube"),
+    # channels for the points (the voxels read are listed) and one too few
+    (8, 2048, 64, 64, 32, 2, "trilinear", "cube"), (16, 2049, 64, 64, 32, 2, "trilinear", "cube"),
+    (16, 513, 16, 64, 32, 1, "trilinear", "shapes"), (16, 512, 16, 64, 32, 1, "trilinear", "shapes"),
+    (8, 9000, 64, 64, 32, 2, "trilinear", "cube"),
     # large clouds: dense grids; more than 512 bricks a cloud
     (1, 65536, 64, 64, 64, 2, "trilinear", "clustered"),
     (1, 5001, 16, 64, 72, 2, "trilinear", "cube"),
