@@ -1426,6 +1426,13 @@ bool pv_conv3d_rows_ok(int B, int R, int Cin, int Cout, int n_convs) {
     // one is listed, small grids do (B = 1, R = 37, 32 channels: 99 us dense,
     // 102 listed; the list costs more than it saves).
     if (n_convs > 2 && rows_small(B, R, Cout)) return false;
+    // Clouds of one whole brick with a CU for every workgroup keep the complete
+    // form: most voxels of eight a side are near a point, the workgroups take
+    // as long as the fullest brick, and listing adds to that (us a layer,
+    // complete and listed: 40 clouds of 256 points, 64 -> 128 twice 74 and 79,
+    // 64 of 64, 64 -> 64 twice 50 and 53; but 80 of 256, 64 -> 128 twice, 320
+    // workgroups, 81 and 72; R = 7 36 and 35; 16 channels 0.97).
+    if (R == kBrick && Cout > 16 && (long)B * ((Cout + 31) / 32) <= 256) return false;
     return Cout % 8 == 0 && Cout <= kRowsMaxCin && pv_conv3d_splits(B, R, Cin, Cout) == 1 &&
            (n_convs < 2 || pv_conv3d_splits(B, R, Cout, Cout) == 1);
 }

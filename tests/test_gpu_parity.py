@@ -975,6 +975,9 @@ def _list_cloud(kind, B, N):
     (5, 777, 9, 64, 16, 2, "trilinear", "cube"),
     (5, 600, 64, 128, 17, 3, "nearest", "shapes"),
     (64, 3, 8, 8, 1, 2, "trilinear", "cube"),
+    # one whole brick a cloud: complete up to 256 workgroups, listed past them
+    (128, 200, 16, 64, 8, 2, "trilinear", "shapes"), (129, 200, 16, 64, 8, 2, "trilinear", "shapes"),
+    (40, 300, 64, 16, 8, 2, "nearest", "cube"), (60, 300, 9, 24, 8, 1, "trilinear", "cube"),
     # channels for the points (the voxels read are listed) and one too few
     (8, 2048, 64, 64, 32, 2, "trilinear", "cube"), (16, 2049, 64, 64, 32, 2, "trilinear", "cube"),
     (16, 513, 16, 64, 32, 1, "trilinear", "shapes"), (16, 512, 16, 64, 32, 1, "trilinear", "shapes"),
