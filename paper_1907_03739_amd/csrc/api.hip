@@ -89,8 +89,8 @@ ForwardWs carve_forward(void* base, int B, int N, const pvconv_layer* L) {
     w.plan = PvConvPlan{};
     if (L->compute_dt == PVCONV_BF16) {
         size_t plan_bytes = 0;
-        pv_conv_plan_carve(nullptr, B, L->R, &plan_bytes);
-        w.plan = pv_conv_plan_carve(take(plan_bytes), B, L->R, &plan_bytes);
+        pv_conv_plan_carve(nullptr, B, L->R, L->n_convs, &plan_bytes);
+        w.plan = pv_conv_plan_carve(take(plan_bytes), B, L->R, L->n_convs, &plan_bytes);
     }
     size_t split = 0;
     if (L->compute_dt == PVCONV_BF16)

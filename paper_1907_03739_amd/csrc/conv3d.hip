@@ -598,9 +598,9 @@ __device__ __forceinline__ void halo_occupied(const int32_t* __restrict__ counts
     }
 }
 
-// list[0], n[0]: D1; list[1], n[1]: the voxels read, which are those holding
-// points (nearest), or the corner cells of the points at pn, or without pn D1
-// (then list[1] is not made).
+// list[0]: D1; list[1]: the voxels read, which are those holding points
+// (nearest), or the corner cells of the points at pn, or without pn D1. A list
+// without a place is not made, nor are D1's bits.
 __global__ __launch_bounds__(256) void pv_conv_plan_kernel(
     const int32_t* __restrict__ counts, const float* __restrict__ pn, int N, int nearest, int R,
     int nbr, PvConvPlan plan) {
@@ -713,7 +713,7 @@ __global__ __launch_bounds__(256) void pv_conv_plan_kernel(
     if (in_row && (tid & 3) == 0) {
         const size_t at = (((size_t)b * R + u0 + ru) * R + v0 + rv) * nbr + bw;
         plan.occ[at] = (uint8_t)occ;
-        plan.d1[at] = (uint8_t)near;
+        if (plan.d1) plan.d1[at] = (uint8_t)near;
     }
     // no occupied voxel in or beside the brick: no point reads it
     if (!__syncthreads_or((int)near)) return;
@@ -730,17 +730,17 @@ __global__ __launch_bounds__(256) void pv_conv_plan_kernel(
             mark(s_near_p[k][0], s_near_p[k][1], s_near_p[k][2]);
         __syncthreads();
     }
-    const int lists = plan.list[1] ? 2 : 1;
-    const uint32_t need[2] = {near, nearest ? occ : s_read[ru * kBrick + rv] & in_w};
+    const uint32_t need[2] = {near, nearest ? occ
+                                            : (pn ? s_read[ru * kBrick + rv] & in_w : near)};
     DealRank d[2];
 #pragma unroll
     for (int q = 0; q < 2; q++)
-        if (q < lists) d[q] = deal_rank(need[q], tid, s_cls[q]);
+        if (plan.list[q]) d[q] = deal_rank(need[q], tid, s_cls[q]);
     __syncthreads();
     int blocks[2] = {0, 0};
 #pragma unroll
     for (int q = 0; q < 2; q++)
-        if (q < lists) blocks[q] = deal_place(d[q], tid, s_cls[q], s_row[q]);
+        if (plan.list[q]) blocks[q] = deal_place(d[q], tid, s_cls[q], s_row[q]);
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < 2; q++) {
@@ -1437,7 +1437,7 @@ bool pv_conv3d_rows_ok(int B, int R, int Cin, int Cout, int n_convs) {
            (n_convs < 2 || pv_conv3d_splits(B, R, Cout, Cout) == 1);
 }
 
-PvConvPlan pv_conv_plan_carve(void* base, int B, int R, size_t* bytes) {
+PvConvPlan pv_conv_plan_carve(void* base, int B, int R, int n_convs, size_t* bytes) {
     const int nbr = (R + kBrick - 1) / kBrick;
     const size_t bricks = (size_t)B * nbr * nbr * nbr;
     size_t off = 0;
@@ -1450,9 +1450,11 @@ PvConvPlan pv_conv_plan_carve(void* base, int B, int R, size_t* bytes) {
     plan.count[0] = (int32_t*)take(kPvPlanCounts * sizeof(int32_t));
     plan.count[1] = plan.count[0] + kPvPlanCounts / 2;
     plan.occ = (uint8_t*)take((size_t)B * R * R * nbr);
-    plan.d1 = (uint8_t*)take((size_t)B * R * R * nbr);
-    plan.n = (uint8_t*)take(bricks);
-    for (int q = 0; q < 2; q++) {
+    if (n_convs == 2) {
+        plan.d1 = (uint8_t*)take((size_t)B * R * R * nbr);
+        plan.n = (uint8_t*)take(bricks);
+    }
+    for (int q = n_convs == 2 ? 0 : 1; q < 2; q++) {
         plan.list[q] = (uint16_t*)take(bricks * kListLen * sizeof(uint16_t));
         plan.order[q] = (int32_t*)take(17 * kPvPlanSub *
                                        ((bricks + kPvPlanSub - 1) / kPvPlanSub) * sizeof(int32_t));
@@ -1480,11 +1482,12 @@ pvconv_status pv_launch_conv_plan(PvConvPlan& plan, const int32_t* counts, const
     const bool small = rows_small(B, R, Cout);
     if (nearest || (long long)B * nb3 * N > (8ll << 20) || (long long)Cin * Cout < 2ll * N)
         pn = nullptr;
-    if (small || (!nearest && !pn)) plan.list[1] = nullptr;
+    const bool one = plan.list[0] && (small || (!nearest && !pn));  // the same list for both
+    if (one) plan.list[1] = nullptr;
     if (!small)
         hipLaunchKernelGGL(pv_conv_plan_kernel, dim3(B * nb3), dim3(256), 0, s, counts, pn, N,
                            (int)nearest, R, nbr, plan);
-    if (!plan.list[1]) {
+    if (one) {
         plan.list[1] = plan.list[0];
         plan.order[1] = plan.order[0];
         plan.count[1] = plan.count[0];

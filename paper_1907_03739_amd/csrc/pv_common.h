@@ -190,7 +190,8 @@ pvconv_status pv_launch_conv3d(const void* x, int B, int R, int Cin, int Cout, c
 // n * kPvPlanSub + s of order[q] holding count[q][..] of them; the
 // kPvPlanCounts words from count[0] have to be zero (PvPackJobs::zero) before
 // the plan is made. Without a plan launch (small grids) the first convolution
-// fills d1, list[0] and n (the blocks of each brick) instead.
+// fills d1, list[0] and n (the blocks of each brick) instead. These three have
+// a place with two convolutions only: no other number reads them.
 constexpr int kPvPlanSub = 8;
 constexpr int kPvPlanCounts = 2 * 17 * kPvPlanSub;
 struct PvConvPlan {
@@ -202,7 +203,7 @@ struct PvConvPlan {
     int32_t* count[2];
 };
 // The plan's arrays in a workspace (256-byte aligned) of *bytes.
-PvConvPlan pv_conv_plan_carve(void* base, int B, int R, size_t* bytes);
+PvConvPlan pv_conv_plan_carve(void* base, int B, int R, int n_convs, size_t* bytes);
 // counts [B][R^3]: the points per voxel; pn [B][N][3]: their normalised
 // coordinates, at whose corner cells (nearest: voxels) the grid is read. Cin,
 // Cout: the last convolution's channels.

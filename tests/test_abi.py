@@ -72,6 +72,13 @@ def test_workspace_queries():
     need = L.pvconv_forward_workspace_size(16, 2048, ctypes.byref(lay))
     # at least: two bf16 grids of 128 channels + the fp32 devox buffer
     assert need >= 2 * 16 * 32 ** 3 * 128 * 2 + 16 * 2048 * 128 * 4
+    # one convolution needs no list of voxels (512 places of 2 bytes a brick) for
+    # a first one beside the last one's
+    two, bricks = need, 16 * 4 ** 3
+    lay.n_convs = 1
+    packed = L.pvconv_conv3d_workspace_size(128, 128, 1)
+    assert L.pvconv_forward_workspace_size(16, 2048, ctypes.byref(lay)) <= \
+        two - packed - bricks * 512 * 2
     lay.n_convs = 0
     assert L.pvconv_forward_workspace_size(16, 2048, ctypes.byref(lay)) == 0
 
