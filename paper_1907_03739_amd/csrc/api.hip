@@ -577,7 +577,7 @@ pvconv_status pvconv_forward_ex(const float* coords, const void* feats, pvconv_d
     // of the normalisation launch (or in a launch of their own when the
     // normalisation is skipped)
     PvPackJobs jobs{};
-    const bool rows = bf && pv_conv3d_rows_ok(B, R, L->cin, L->cout, L->n_convs);
+    const bool rows = bf && pv_conv3d_rows_ok(B, N, R, L->cin, L->cout, L->n_convs);
     if (rows) {
         jobs.zero = w.plan.count[0];
         jobs.nzero = kPvPlanCounts;

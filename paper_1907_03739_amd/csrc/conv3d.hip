@@ -1420,7 +1420,7 @@ pvconv_status pv_launch_conv3d(const void* x, int B, int R, int Cin, int Cout, c
     return pv_launch_status();
 }
 
-bool pv_conv3d_rows_ok(int B, int R, int Cin, int Cout, int n_convs) {
+bool pv_conv3d_rows_ok(int B, int N, int R, int Cin, int Cout, int n_convs) {
     // Grids so small that the dense convolution splits its input channels
     // keep that form, and with three or more convolutions, where only the last
     // one is listed, small grids do (B = 1, R = 37, 32 channels: 99 us dense,
@@ -1433,7 +1433,15 @@ bool pv_conv3d_rows_ok(int B, int R, int Cin, int Cout, int n_convs) {
     // 64 of 64, 64 -> 64 twice 50 and 53; but 80 of 256, 64 -> 128 twice, 320
     // workgroups, 81 and 72; R = 7 36 and 35; 16 channels 0.97).
     if (R == kBrick && Cout > 16 && (long)B * ((Cout + 31) / 32) <= 256) return false;
-    return Cout % 8 == 0 && Cout <= kRowsMaxCin && pv_conv3d_splits(B, R, Cin, Cout) == 1 &&
+    // More channels than the table of constants holds, which only a second
+    // convolution reads: a single one of 512 tiles and more, from clouds whose
+    // grids stay sparse (us a layer, complete and listed: 16 clouds of 2048
+    // points, R = 32, 64 -> 512 481 and 214; 128 of 4096, R = 8, 64 -> 320 614
+    // and 608; but one of 65536, R = 32, 64 -> 512 178 and 276).
+    if (Cout > kRowsMaxCin &&
+        (n_convs > 1 || rows_small(B, R, Cout) || !pv_voxelize_sparse_ok(N)))
+        return false;
+    return Cout % 8 == 0 && pv_conv3d_splits(B, R, Cin, Cout) == 1 &&
            (n_convs < 2 || pv_conv3d_splits(B, R, Cout, Cout) == 1);
 }
 

@@ -227,7 +227,7 @@ struct PvConvRows {
     } input;             // batch norm bn_in and the same activation
     PvBnFold bn_in;
 };
-bool pv_conv3d_rows_ok(int B, int R, int Cin, int Cout, int n_convs);
+bool pv_conv3d_rows_ok(int B, int N, int R, int Cin, int Cout, int n_convs);
 pvconv_status pv_launch_conv3d_rows(const PvConvRows& c, const PvBnFold& bn, int act, float slope,
                                     hipStream_t s);
 int pv_conv3d_splits(int B, int R, int Cin, int Cout);

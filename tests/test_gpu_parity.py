@@ -982,6 +982,11 @@ def _list_cloud(kind, B, N):
     (8, 2048, 64, 64, 32, 2, "trilinear", "cube"), (16, 2049, 64, 64, 32, 2, "trilinear", "cube"),
     (16, 513, 16, 64, 32, 1, "trilinear", "shapes"), (16, 512, 16, 64, 32, 1, "trilinear", "shapes"),
     (8, 9000, 64, 64, 32, 2, "trilinear", "cube"),
+    # a single convolution of more channels than the constants' table holds:
+    # listed, and complete for its width, its few tiles, its large clouds
+    (8, 1500, 64, 320, 32, 1, "trilinear", "shapes"), (16, 800, 16, 512, 16, 1, "nearest", "cube"),
+    (4, 700, 16, 264, 32, 1, "trilinear", "shapes"), (2, 700, 16, 320, 16, 1, "trilinear", "cube"),
+    (2, 5000, 16, 320, 32, 1, "trilinear", "cube"),
     # large clouds: dense grids; more than 512 bricks a cloud
     (1, 65536, 64, 64, 64, 2, "trilinear", "clustered"),
     (1, 5001, 16, 64, 72, 2, "trilinear", "cube"),
