@@ -773,8 +773,8 @@ __global__ __launch_bounds__(256) void pv_conv_plan_kernel(
 // on alone for a third of the time.
 // SELF (counts given): the workgroup makes its brick's D1 list itself, and
 // the first tile's stores it and D1's bits in `made` for the next convolution.
-// For grids whose workgroups are all resident at once, where the order is of
-// no use and the plan's launch (5 to 6 us) costs more than it saves.
+// For the grids and widths of rows_small, where the order is of little use and
+// the plan's launch (5 to 6 us) costs more than it saves.
 // Input modes: bits says which rows exist; the others are zero, or with KONST
 // (the output of such a convolution, bits D1) the constant of its batch norm
 // bn_in, or with dense exist too.
@@ -1295,8 +1295,18 @@ void launch_rows(const PvConvRows& c, const PvBnFold& bn, float neg, bool vec, h
 #undef PV_ROWS_CONV
 }
 
-// Grids of fewer than 512 tiles of 64 channels (two a CU) take 32-channel
-// tiles and no plan: their workgroups are resident at once.
+// No plan, 32-channel tiles:
+//  * grids of fewer than 512 tiles of 64 channels (two a CU), whose workgroups
+//    are about all resident at once;
+//  * widths that are no multiple of 64, on grids of any size. Their workgroups
+//    are not all resident on large grids, every tile lists its brick again,
+//    and the last convolution computes D1; but a plan with 32-channel tiles
+//    gains only from three tiles a brick on (us a layer of two convolutions,
+//    this form, the plan's and the complete grid, 16 clouds of 2048 points at
+//    R = 32: 16 -> 16 66, 73, 99; 24 -> 24 77, 80, 117; 32 -> 32 80, 82, 115; 24
+//    -> 40 107, 104, 211; 48 -> 48 119, 115, 234; 96 -> 96 225, 197, 491; 64
+//    clouds: 32 -> 32 233, 230, 393; 32 -> 96 628, 544, 1564). With 96 channels
+//    and more on large grids this form gives away an eighth.
 bool rows_small(int B, int R, int Cout) {
     const int nbr = (R + kBrick - 1) / kBrick;
     return Cout % 64 != 0 || (long)B * nbr * nbr * nbr * (Cout / 64) < 512;
@@ -1423,15 +1433,19 @@ pvconv_status pv_launch_conv3d(const void* x, int B, int R, int Cin, int Cout, c
 bool pv_conv3d_rows_ok(int B, int N, int R, int Cin, int Cout, int n_convs) {
     // Grids so small that the dense convolution splits its input channels
     // keep that form, and with three or more convolutions, where only the last
-    // one is listed, small grids do (B = 1, R = 37, 32 channels: 99 us dense,
-    // 102 listed; the list costs more than it saves).
+    // one is listed, so do all that rows_small names (B = 1, R = 37, 32
+    // channels: 99 us dense, 102 listed; the list costs more than it saves. Not
+    // so on large grids of widths that are no multiple of 64, whose form
+    // without a plan is then not used either: 16 clouds of 2048 points at R =
+    // 32, 32 -> 32 156 us dense, 150 with a plan, 32 -> 96 629, 489).
     if (n_convs > 2 && rows_small(B, R, Cout)) return false;
     // Clouds of one whole brick with a CU for every workgroup keep the complete
     // form: most voxels of eight a side are near a point, the workgroups take
     // as long as the fullest brick, and listing adds to that (us a layer,
-    // complete and listed: 40 clouds of 256 points, 64 -> 128 twice 74 and 79,
-    // 64 of 64, 64 -> 64 twice 50 and 53; but 80 of 256, 64 -> 128 twice, 320
-    // workgroups, 81 and 72; R = 7 36 and 35; 16 channels 0.97).
+    // complete and listed: 40 clouds of 256 points, 64 -> 128 twice, 61.6 and
+    // 65.7; 64 of 64, 64 -> 64 twice, 49.8 and 53.4; but 80 of 256, 64 -> 128
+    // twice, 320 workgroups, 107 and 97; 40 of 256 at R = 7 62.2 and 59.6, at R
+    // = 8 16 -> 16 41.2 and 40.1).
     if (R == kBrick && Cout > 16 && (long)B * ((Cout + 31) / 32) <= 256) return false;
     // More channels than the table of constants holds, which only a second
     // convolution reads: a single one of 512 tiles and more, from clouds whose
