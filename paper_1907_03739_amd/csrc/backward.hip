@@ -454,7 +454,10 @@ __device__ __forceinline__ int pv_div_small(int x, int d, float inv, int* rem) {
 // 4096 such workgroups take one turn; larger ones, mostly zeros, take up to
 // four. Whole calls, us, before and now: 3 clouds of 1500 points at R = 16, 64
 // channels 68 and 27; 8 of 2048 at R = 32, 128 channels (134 MB written) 79
-// and 59 (66 with one turn); 65536 clustered points at R = 64 899 and 873.
+// and 59 (66 with one turn); 30000 clustered points at R = 32 727 and 495; 65536
+// at R = 64, whose fullest cells' chains are the call, 800 to 1010 and 860 to
+// 1020 by the cloud (a chain's step finds its range among eight, which costs a
+// long chain what the shared latencies save it).
 template <int VW, bool NEAREST>
 __global__ __launch_bounds__(256) void pv_devox_bwd_gather_kernel(
     const float* __restrict__ srow, const float* __restrict__ rec_w,
