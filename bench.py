@@ -17,7 +17,8 @@ Default workload: the part-segmentation-scale layer, 16 clouds x 2048 points,
 
 Printed: ONE JSON line with the headline throughput (points/s), ms per layer,
 the roofline of the dominant kernel (the convolution, MFMA-bound, timed on
-weights packed beforehand as the forward runs it), per-step timings of the
+weights packed beforehand; on complete grids, where the forward multiplies
+lists of voxels), per-step timings of the
 same chain (back to back, and cold: after a 512 MiB write that evicts the
 caches), including the fused devoxelisation + point MLP kernel the forward
 runs, the peak device memory of one forward, the device's measured peaks (a
@@ -828,6 +829,7 @@ def bench_layer(args, wl, dev, cold=True, peaks=True, cpu_seconds=None):
                                  "zero rows (its first convolution reads them as zero through "
                                  "the counts) and with the weight packing in extra workgroups")
         if bf16 and n.startswith("conv") and L.n_convs <= 2:
+            k["in_forward"] = False
             k["forward_form"] = ("the forward lists the voxels that are read and multiplies "
                                  "those alone (pv_conv_plan_kernel, pv_conv3d_rows_kernel); "
                                  "timed here is the complete grid")
@@ -856,6 +858,10 @@ def bench_layer(args, wl, dev, cold=True, peaks=True, cpu_seconds=None):
                 "flop_per_launch": conv_work, "avg_launch_ms": round(conv_ms, 4),
                 "timed": "pvconv_conv3d_packed (weights packed beforehand)" if bf16 else
                          "pvconv_conv3d"}
+    if "forward_form" in kernels[conv_names[0]]:
+        # the complete grid, which the timed step does not launch
+        roofline["in_forward"] = False
+        roofline["forward_form"] = kernels[conv_names[0]]["forward_form"]
     if pk and bf16:
         roofline["frac_measured_peak"] = round(achieved / pk["mfma_bf16_tflops"], 4)
 
@@ -887,7 +893,8 @@ def bench_layer(args, wl, dev, cold=True, peaks=True, cpu_seconds=None):
 
 def compact(line):
     """The summary of one workload's line kept in the headline's `workloads`."""
-    ks = {n: k for n, k in line["kernels"].items() if k.get("in_forward", True)}
+    ks = {n: k for n, k in line["kernels"].items()
+          if k.get("in_forward", True) or "forward_form" in k}
     dom = max(ks, key=lambda n: ks[n]["ms"])
     out = {"workload": line["config"]["workload"], "dtype": line["dtype"],
            "points_per_step": line["config"]["points_per_step"],
