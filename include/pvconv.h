@@ -240,7 +240,8 @@ pvconv_status pvconv_devoxelize_nearest(const void* grid, int B, int R, int C,
 /*             + residual[m,o]                                               */
 /* where P = points_per_cloud. Rows m = 0..M-1.                              */
 /*  x           [M][Cin] (x_dt), row stride x_ld                             */
-/*  weight      [Cout][Cin] (compute_dt: BF16 -> MFMA, F32 -> fp32 FMA)      */
+/*  weight      [Cout][Cin] (compute_dt: BF16 -> MFMA; F32 -> the fp32 MFMA, */
+/*              or fp32 FMA for few channels: fp32 products and sums)        */
 /*  bias        [Cout] fp32 or NULL; bn may be NULL                          */
 /*  cloud_bias  [M/P][Cout] fp32 or NULL (a per-cloud row, e.g. the          */
 /*              projection of a broadcast global feature)                    */
